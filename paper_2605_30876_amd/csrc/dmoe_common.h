@@ -198,6 +198,8 @@ struct FfnArgs {
   void* workspace;  // SwiGLU activations of T*k (+ T) rows, max(I, I_s) wide, storage type
 };
 hipError_t launch_ffn(const FfnArgs& a, dmoe_dtype dt, hipStream_t s);
+// The fp32 kernels: ldh = max(I, I_s), items = max_work + the shared pieces.
+hipError_t launch_ffn_f32(const FfnArgs& a, int ldh, int items, hipStream_t s);
 // Device address of this device's DMOE_NOALLOC_SCRATCH_BYTES scratch array
 // (looked up on the first call per device, then cached).
 hipError_t noalloc_scratch(void** ptr);

@@ -39,8 +39,7 @@
 //    row in both operands, which is all the matrix instruction needs.
 //    Scattered token rows (token-level routing) may instead be read from the
 //    row-major x, one 64-byte piece per token and K-step (tile_gathered).
-// f32 path: reduction-major weights, each lane one output unit, the waves
-// splitting the reduction (small fp32 layers).
+// fp32 layers: ffn_f32.hip.
 #include <algorithm>
 #include <type_traits>
 
@@ -52,46 +51,8 @@ namespace {
 
 constexpr int kThreads = 256;
 
-struct Group {
-  int r0;          // first row of the item in the row space (h buffer row)
-  int n;           // rows (tokens) in the item
-  int expert;      // routed expert id, or -1 for the shared expert
-  const int* tok;  // token of each row (routed), or nullptr: row c is token t0 + c
-  int t0;
-  int piece;       // index of the item among its expert's items (0, 1, ...)
-};
-
-// Grid row y: the schedule's max_work items, then the shared expert's pieces
-// (kSharedFirst: the pieces first).  One memory round trip: the item count
-// and the item are loaded together (the index stays inside the work array;
-// an item past n_work is loaded but not used).  An item naming an expert
-// outside [0, E) is skipped, so no schedule can steer a weight read outside
-// the expert arrays.
-template <bool kSharedFirst = false>
-__device__ __forceinline__ bool decode_item(int y, int shared_items, int max_work, const int* n_work,
-                                            const int* work, const int* row_token, int T, int Tk, int E, Group& g) {
-  const int w = kSharedFirst ? y - shared_items : y;
-  if (kSharedFirst ? w >= 0 : w < max_work) {
-    const int nw = *n_work;
-    const int4 it = reinterpret_cast<const int4*>(work)[w];
-    g.expert = it.x;
-    g.r0 = it.y;
-    g.n = (w < nw && static_cast<unsigned>(it.x) < static_cast<unsigned>(E)) ? it.z : 0;
-    g.tok = row_token + it.y;
-    g.t0 = 0;
-    g.piece = it.w;
-  } else {
-    const int c = kSharedFirst ? y : y - max_work;
-    g.expert = -1;
-    g.piece = c;
-    g.t0 = c * DMOE_WORK_ROWS;
-    g.r0 = Tk + g.t0;
-    g.n = min(DMOE_WORK_ROWS, T - g.t0);
-    g.tok = nullptr;
-  }
-  return g.n > 0;
-}
-
+using fdev::decode_item;
+using fdev::Group;
 // ---- bf16 kernels ----------------------------------------------------------
 
 // Which copy of x serves a token tile's B loads better.  Lane (q, c) of
@@ -527,141 +488,6 @@ __global__ __launch_bounds__(kThreads, 2) void ffn_tile_bf16_kernel(FfnParams p,
     tile_body<kGateUp, kRowTiles, false>(p, g, bx, stage);
 }
 
-// ---- f32 path -------------------------------------------------------------
-//
-// Weights are reduction-major (w13[e][h][u], w2[e][i][j]), so the 64 lanes of
-// a wave, one output unit each, read 256 contiguous bytes per reduction
-// index.  The four waves of a workgroup split the reduction in quarters and
-// keep kF32Tok tokens' partial sums in registers; the token values are the
-// same for every lane (scalar loads).  Partial sums are added in wave order
-// through LDS.
-
-constexpr int kF32Tok = 8;  // tokens per pass
-
-// grid (ceil(max(I, I_s) / 64), groups): units 64*bx + lane of item g.
-__global__ __launch_bounds__(kThreads) void ffn_gateup_f32_kernel(
-    const float* __restrict__ xk, const float* __restrict__ w13, const float* __restrict__ ws13,
-    const int* __restrict__ n_work, const int* __restrict__ work, const int* __restrict__ row_token, int T, int H,
-    int E, int I, int I_s, int Tk, int max_work, int ldh, float* __restrict__ hbuf) {
-  Group g;
-  if (!decode_item(blockIdx.y, 0, max_work, n_work, work, row_token, T, Tk, E, g)) return;
-  const int Iw = g.expert >= 0 ? I : I_s;
-  if (static_cast<int>(blockIdx.x) * kWave >= Iw) return;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int u = blockIdx.x * kWave + lane;
-  const bool live = u < Iw;
-  const int uc = live ? u : Iw - 1;
-  const float* W = g.expert >= 0 ? w13 + static_cast<size_t>(g.expert) * 2 * I * H : ws13;
-  const size_t ldw = 2 * static_cast<size_t>(Iw);
-  const int nch = H >> 2, per = (nch + 3) >> 2;  // 4-feature chunks, a quarter per wave
-  const int c0 = wave * per, c1 = min(nch, c0 + per);
-  __shared__ float red[3][2][kF32Tok][kWave];
-  for (int p0 = 0; p0 < g.n; p0 += kF32Tok) {
-    float ag[kF32Tok], au[kF32Tok];
-    int tok[kF32Tok];
-#pragma unroll
-    for (int t = 0; t < kF32Tok; ++t) {
-      ag[t] = au[t] = 0.f;
-      const int col = min(p0 + t, g.n - 1);
-      tok[t] = g.tok ? g.tok[col] : g.t0 + col;
-    }
-#pragma unroll 4
-    for (int c = c0; c < c1; ++c) {
-      float wg[4], wu[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const float* wr = W + static_cast<size_t>(4 * c + q) * ldw;
-        wg[q] = wr[uc];
-        wu[q] = wr[Iw + uc];
-      }
-#pragma unroll
-      for (int t = 0; t < kF32Tok; ++t) {
-        const f32x4 xv = *reinterpret_cast<const f32x4*>(xk + (static_cast<size_t>(c) * T + tok[t]) * 4);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          ag[t] = fmaf(xv[q], wg[q], ag[t]);
-          au[t] = fmaf(xv[q], wu[q], au[t]);
-        }
-      }
-    }
-    if (wave > 0) {
-#pragma unroll
-      for (int t = 0; t < kF32Tok; ++t) {
-        red[wave - 1][0][t][lane] = ag[t];
-        red[wave - 1][1][t][lane] = au[t];
-      }
-    }
-    __syncthreads();
-    if (wave == 0) {
-#pragma unroll
-      for (int t = 0; t < kF32Tok; ++t) {
-#pragma unroll
-        for (int ww = 0; ww < 3; ++ww) {
-          ag[t] += red[ww][0][t][lane];
-          au[t] += red[ww][1][t][lane];
-        }
-        if (live && p0 + t < g.n) hbuf[static_cast<size_t>(g.r0 + p0 + t) * ldh + u] = silu_f32(ag[t]) * au[t];
-      }
-    }
-    __syncthreads();  // red is reused by the next pass
-  }
-}
-
-// grid (ceil(H / 64), groups): output features 64*bx + lane of item g.
-__global__ __launch_bounds__(kThreads) void ffn_down_f32_kernel(
-    const float* __restrict__ w2, const float* __restrict__ ws2, const int* __restrict__ n_work,
-    const int* __restrict__ work, const int* __restrict__ row_token, const int* __restrict__ row_slot, int T,
-    int H, int E, int I, int I_s, int k, int Tk, int max_work, int ldh, const float* __restrict__ hbuf,
-    float* __restrict__ slot_out, float* __restrict__ shared_out) {
-  Group g;
-  if (!decode_item(blockIdx.y, 0, max_work, n_work, work, row_token, T, Tk, E, g)) return;
-  const int Kd = g.expert >= 0 ? I : I_s;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int j = blockIdx.x * kWave + lane;
-  const bool live = j < H;
-  const int jc = live ? j : H - 1;
-  const float* W = g.expert >= 0 ? w2 + static_cast<size_t>(g.expert) * H * I : ws2;
-  const int per = (Kd + 3) >> 2;
-  const int i0 = wave * per, i1 = min(Kd, i0 + per);
-  __shared__ float red[3][kF32Tok][kWave];
-  for (int p0 = 0; p0 < g.n; p0 += kF32Tok) {
-    float acc[kF32Tok];
-    const float* hr[kF32Tok];
-#pragma unroll
-    for (int t = 0; t < kF32Tok; ++t) {
-      acc[t] = 0.f;
-      hr[t] = hbuf + static_cast<size_t>(g.r0 + min(p0 + t, g.n - 1)) * ldh;
-    }
-#pragma unroll 8
-    for (int i = i0; i < i1; ++i) {
-      const float wv = W[static_cast<size_t>(i) * H + jc];
-#pragma unroll
-      for (int t = 0; t < kF32Tok; ++t) acc[t] = fmaf(hr[t][i], wv, acc[t]);
-    }
-    if (wave > 0) {
-#pragma unroll
-      for (int t = 0; t < kF32Tok; ++t) red[wave - 1][t][lane] = acc[t];
-    }
-    __syncthreads();
-    if (wave == 0) {
-#pragma unroll
-      for (int t = 0; t < kF32Tok; ++t) {
-#pragma unroll
-        for (int ww = 0; ww < 3; ++ww) acc[t] += red[ww][t][lane];
-        const int col = p0 + t;
-        if (!live || col >= g.n) continue;
-        if (g.tok) {
-          const int r = g.r0 + col;
-          slot_out[(static_cast<size_t>(row_token[r]) * k + row_slot[r]) * H + j] = acc[t];
-        } else {
-          shared_out[static_cast<size_t>(g.t0 + col) * H + j] = acc[t];
-        }
-      }
-    }
-    __syncthreads();
-  }
-}
-
 // ---- launch ---------------------------------------------------------------
 
 // Token columns per pass: enough 16-wide tiles for the expected rows of a
@@ -808,18 +634,7 @@ hipError_t launch_ffn(const FfnArgs& a, dmoe_dtype dt, hipStream_t s) {
       default: return launch_bf16<4>(p, ldh, items, s);
     }
   }
-  float* hbuf = static_cast<float*>(a.workspace);
-  dim3 g_gu((ldh + kWave - 1) / kWave, items), g_dn((a.H + kWave - 1) / kWave, items);
-  ffn_gateup_f32_kernel<<<g_gu, kThreads, 0, s>>>(
-      static_cast<const float*>(a.x), static_cast<const float*>(a.w13), static_cast<const float*>(a.ws13),
-      a.sched.n_work, a.sched.work, a.sched.row_token, a.T, a.H, a.E, a.I, a.I_s, Tk, a.max_work, ldh, hbuf);
-  hipError_t err = hipGetLastError();
-  if (err != hipSuccess) return err;
-  ffn_down_f32_kernel<<<g_dn, kThreads, 0, s>>>(
-      static_cast<const float*>(a.w2), static_cast<const float*>(a.ws2), a.sched.n_work, a.sched.work,
-      a.sched.row_token, a.sched.row_slot, a.T, a.H, a.E, a.I, a.I_s, a.k, Tk, a.max_work, ldh, hbuf,
-      static_cast<float*>(a.slot_out), a.shared_out);  // f32 layers: float32 slot outputs (checked by the API)
-  return hipGetLastError();
+  return launch_ffn_f32(a, ldh, items, s);
 }
 
 }  // namespace dmoe

@@ -9,6 +9,46 @@
 namespace dmoe {
 namespace fdev {
 
+struct Group {
+  int r0;          // first row of the item in the row space (h buffer row)
+  int n;           // rows (tokens) in the item
+  int expert;      // routed expert id, or -1 for the shared expert
+  const int* tok;  // token of each row (routed), or nullptr: row c is token t0 + c
+  int t0;
+  int piece;       // index of the item among its expert's items (0, 1, ...)
+};
+
+// Grid row y: the schedule's max_work items, then the shared expert's pieces
+// (kSharedFirst: the pieces first).  One memory round trip: the item count
+// and the item are loaded together (the index stays inside the work array;
+// an item past n_work is loaded but not used).  An item naming an expert
+// outside [0, E) is skipped, so no schedule can steer a weight read outside
+// the expert arrays.
+template <bool kSharedFirst = false>
+__device__ __forceinline__ bool decode_item(int y, int shared_items, int max_work, const int* n_work,
+                                            const int* work, const int* row_token, int T, int Tk, int E, Group& g) {
+  const int w = kSharedFirst ? y - shared_items : y;
+  if (kSharedFirst ? w >= 0 : w < max_work) {
+    const int nw = *n_work;
+    const int4 it = reinterpret_cast<const int4*>(work)[w];
+    g.expert = it.x;
+    g.r0 = it.y;
+    g.n = (w < nw && static_cast<unsigned>(it.x) < static_cast<unsigned>(E)) ? it.z : 0;
+    g.tok = row_token + it.y;
+    g.t0 = 0;
+    g.piece = it.w;
+  } else {
+    const int c = kSharedFirst ? y : y - max_work;
+    g.expert = -1;
+    g.piece = c;
+    g.t0 = c * DMOE_WORK_ROWS;
+    g.r0 = Tk + g.t0;
+    g.n = min(DMOE_WORK_ROWS, T - g.t0);
+    g.tok = nullptr;
+  }
+  return g.n > 0;
+}
+
 constexpr int kFrag = 512;  // bf16 elements of one packed 16 x 32 weight tile (1 KiB)
 
 // Operands of one wave for up to KMAX K-steps (32 each) of its K-slice.

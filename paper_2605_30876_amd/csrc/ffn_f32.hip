@@ -1,0 +1,361 @@
+// Expert execution of fp32 layers (the fp32 counterpart of ffn.hip): the
+// SwiGLU FFN of every work item and of the shared expert's pieces.
+//
+// Both products run on the fp32 matrix cores (v_mfma_f32_16x16x4_f32: fp32
+// operands, products and sums, like a chain of fused multiply-adds).  The
+// weights are reduction-major (w13[e][h][u], w2[e][i][j]), so one 16-lane row
+// of a wave reads U consecutive output units per lane of one reduction index
+// (U = 4: 256 contiguous bytes) and the four 16-lane rows four indices; lane
+// (q, c) thereby holds the matrix operand of units u0 + U*c .. + U-1 at
+// reduction index 16*g + 4*q + i for i = 0..3 (four loads), and the token
+// operand of the same four indices is one 16-byte load of its token's
+// values.  The order in which a matrix instruction sums its indices does not
+// matter as long as both operands agree, so neither is rearranged.
+//
+// What bounds it: the weight stream.  A forward of few tokens reads each
+// selected expert's weights once; a workgroup covers 16*U units, its four
+// waves split the reduction (summed in wave order through LDS, so results do
+// not depend on scheduling) and keep two bursts of weights in flight each.
+// The scalar-FMA kernels this replaces kept eight tokens per pass, one
+// dependent chain of loads per pass: two blocks of 32 tokens over 32 experts
+// (hidden 1024, intermediate 512, top-4, token routing) took 344 + 122 us for
+// gate/up + down, 207 MB at 0.45 TB/s.
+#include <algorithm>
+
+#include "dmoe_common.h"
+#include "ffn_dev.h"
+
+namespace dmoe {
+namespace {
+
+using fdev::decode_item;
+using fdev::Group;
+
+constexpr int kThreads = 256;
+constexpr int kWaves = kThreads / kWave;
+constexpr int kGroup = 16;  // reduction indices of one group: four per 16-lane row
+constexpr int kBurst = 2;   // groups loaded together; two bursts are in flight
+
+struct F32Params {
+  const float* xk;  // activations, chunk-major [H/4][T][4]
+  const float *w13, *w2, *ws13, *ws2;
+  const int *n_work, *work, *row_token, *row_slot;
+  int T, H, E, I, I_s, k, Tk, max_work, ldh;
+  float* hbuf;      // SwiGLU activations [Tk (+ T)][ldh]
+  float* slot_out;  // [T][k][H]
+  float* shared_out;
+};
+
+// One burst of a wave's operands: NM weight matrices (gate and up, or down
+// alone), NT tiles of 16 tokens.
+template <int U, int NM, int NT>
+struct Burst {
+  float a[kBurst][4][NM][U];
+  f32x4 b[kBurst][NT];
+};
+
+template <int U, bool kStream>
+__device__ __forceinline__ void ld_units(const float* p, float (&v)[U]) {
+  if constexpr (U == 4) {
+    const f32x4* p4 = reinterpret_cast<const f32x4*>(p);
+    const f32x4 x = kStream ? __builtin_nontemporal_load(p4) : *p4;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = x[u];
+  } else {
+    static_assert(U == 1, "units per lane");
+    v[0] = kStream ? __builtin_nontemporal_load(p) : *p;
+  }
+}
+
+template <int U, int NM, int NT>
+__device__ __forceinline__ void mma_group(const float (&a)[4][NM][U], const f32x4 (&b)[NT], f32x4 (&acc)[NM][U][NT]) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int m = 0; m < NM; ++m)
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int ct = 0; ct < NT; ++ct)
+          acc[m][u][ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][m][u], b[ct][i], acc[m][u][ct], 0, 0, 0);
+}
+
+// acc += W . B over the reduction groups g0 .. g1-1 of a reduction of length
+// K.  pw[m]: matrix m at this lane's units, index 4*q; row stride ldw.
+// pb[ct]: token tile ct's values at index 4*q; bstep elements to the next
+// group; kVecB: its four values are one aligned 16-byte load.  Groups past
+// the end of a burst reload the last one (straight-line loads) and are not
+// used; a last group that K does not fill is loaded element by element, with
+// zeros past K in both operands.
+template <int U, int NM, int NT, bool kStream, bool kVecB>
+__device__ __forceinline__ void wave_dot_f32(const float* const (&pw)[NM], size_t ldw, const float* const (&pb)[NT],
+                                             int bstep, int K, int g0, int g1, int q, f32x4 (&acc)[NM][U][NT]) {
+  const int nfull = K / kGroup;
+  const int ge = min(g1, nfull);
+  Burst<U, NM, NT> r[2];
+  auto load = [&](Burst<U, NM, NT>& d, int g) {
+#pragma unroll
+    for (int s = 0; s < kBurst; ++s) {
+      const int gs = min(g + s, ge - 1);
+      const size_t row = static_cast<size_t>(gs) * kGroup;
+#pragma unroll
+      for (int ct = 0; ct < NT; ++ct) {
+        const float* p = pb[ct] + static_cast<size_t>(gs) * bstep;
+        if constexpr (kVecB)
+          d.b[s][ct] = *reinterpret_cast<const f32x4*>(p);
+        else
+#pragma unroll
+          for (int i = 0; i < 4; ++i) d.b[s][ct][i] = p[i];
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int m = 0; m < NM; ++m) ld_units<U, kStream>(pw[m] + (row + i) * ldw, d.a[s][i][m]);
+    }
+  };
+  auto mma = [&](const Burst<U, NM, NT>& d, int g) {
+#pragma unroll
+    for (int s = 0; s < kBurst; ++s)
+      if (g + s < ge) mma_group<U, NM, NT>(d.a[s], d.b[s], acc);  // uniform
+  };
+  if (g0 < ge) {
+    load(r[0], g0);
+    for (int g = g0; g < ge; g += 2 * kBurst) {
+      load(r[1], g + kBurst);
+      __builtin_amdgcn_sched_barrier(0);
+      mma(r[0], g);
+      __builtin_amdgcn_sched_barrier(0);
+      load(r[0], g + 2 * kBurst);
+      __builtin_amdgcn_sched_barrier(0);
+      mma(r[1], g + kBurst);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  if (K % kGroup && g0 <= nfull && nfull < g1) {  // uniform: the wave that owns the partial group
+    float a[4][NM][U];
+    f32x4 b[NT];
+    const size_t row = static_cast<size_t>(nfull) * kGroup;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const bool in = static_cast<int>(row) + 4 * q + i < K;
+#pragma unroll
+      for (int m = 0; m < NM; ++m) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) a[i][m][u] = in ? pw[m][(row + i) * ldw + u] : 0.f;
+      }
+#pragma unroll
+      for (int ct = 0; ct < NT; ++ct) b[ct][i] = in ? pb[ct][static_cast<size_t>(nfull) * bstep + i] : 0.f;
+    }
+    mma_group<U, NM, NT>(a, b, acc);
+  }
+}
+
+// Sum the four waves' partial tiles into wave 0's registers (wave order).
+template <int U, int NM, int NT>
+__device__ __forceinline__ void reduce_waves_f32(f32x4 (&acc)[NM][U][NT], f32x4* red, int wave, int lane) {
+  constexpr int kTiles = NM * U * NT;
+  if (wave > 0) {
+#pragma unroll
+    for (int m = 0; m < NM; ++m)
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int ct = 0; ct < NT; ++ct) red[((wave - 1) * kTiles + (m * U + u) * NT + ct) * kWave + lane] = acc[m][u][ct];
+  }
+  __syncthreads();
+  if (wave == 0) {
+#pragma unroll
+    for (int m = 0; m < NM; ++m)
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int ct = 0; ct < NT; ++ct)
+#pragma unroll
+          for (int w = 0; w < kWaves - 1; ++w) acc[m][u][ct] += red[(w * kTiles + (m * U + u) * NT + ct) * kWave + lane];
+  }
+}
+
+template <int U, int NM, int NT>
+__device__ __forceinline__ void zero_f32(f32x4 (&acc)[NM][U][NT]) {
+#pragma unroll
+  for (int m = 0; m < NM; ++m)
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int ct = 0; ct < NT; ++ct) acc[m][u][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+}
+
+// One pass of the gate/up kernel: 16*NT rows of the item from row p0.
+template <int U, int NT, bool kStream>
+__device__ __forceinline__ void gateup_pass(const F32Params& p, const Group& g, int Iw, int u0, int p0, f32x4* red) {
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, q = lane >> 4, c = lane & 15;
+  const float* W = g.expert >= 0 ? p.w13 + static_cast<size_t>(g.expert) * 2 * p.I * p.H : p.ws13;
+  const size_t ldw = 2 * static_cast<size_t>(Iw);
+  const int uc = min(u0 + U * c, Iw - U);  // units past the last: the last ones again, not stored
+  const float* const pw[2] = {W + 4 * q * ldw + uc, W + 4 * q * ldw + Iw + uc};
+  const float* pb[NT];
+#pragma unroll
+  for (int ct = 0; ct < NT; ++ct) {
+    const int col = min(p0 + ct * 16 + c, g.n - 1);
+    const int tok = g.tok ? g.tok[col] : g.t0 + col;
+    pb[ct] = p.xk + (static_cast<size_t>(q) * p.T + tok) * 4;
+  }
+  const int ng = (p.H + kGroup - 1) / kGroup, per = (ng + kWaves - 1) / kWaves;
+  f32x4 acc[2][U][NT];
+  zero_f32(acc);
+  wave_dot_f32<U, 2, NT, kStream, true>(pw, ldw, pb, 16 * p.T, p.H, wave * per, min(ng, (wave + 1) * per), q, acc);
+  reduce_waves_f32(acc, red, wave, lane);
+  if (wave == 0) {
+    // accumulator r of lane (q, c): units u0 + U*(4q + r) + u of row p0 + 16ct + c
+#pragma unroll
+    for (int ct = 0; ct < NT; ++ct) {
+      const int col = p0 + ct * 16 + c;
+      if (col >= g.n) continue;
+      float* dst = p.hbuf + static_cast<size_t>(g.r0 + col) * p.ldh;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int u1 = u0 + U * (4 * q + r);
+        float h[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) h[u] = silu_f32(acc[0][u][ct][r]) * acc[1][u][ct][r];
+        if constexpr (U == 4) {
+          if (u1 < Iw) *reinterpret_cast<f32x4*>(dst + u1) = f32x4{h[0], h[1], h[2], h[3]};  // I % 4 == 0
+        } else {
+          if (u1 < Iw) dst[u1] = h[0];
+        }
+      }
+    }
+  }
+  __syncthreads();  // red is reused by the next pass
+}
+
+// grid (ceil(ldh / (16 U)), items): units 16*U*bx .. of item y.  U = 4 needs
+// I % 4 == 0 and I_s % 4 == 0 (aligned 16-byte loads and stores).
+template <int U, bool kStream>
+__global__ __launch_bounds__(kThreads, 2) void ffn_gateup_f32_kernel(F32Params p) {
+  __shared__ f32x4 red[(kWaves - 1) * 2 * U * 2 * kWave];
+  Group g;
+  if (!decode_item(blockIdx.y, 0, p.max_work, p.n_work, p.work, p.row_token, p.T, p.Tk, p.E, g)) return;
+  const int Iw = g.expert >= 0 ? p.I : p.I_s;
+  const int u0 = blockIdx.x * 16 * U;
+  if (u0 >= Iw) return;
+  for (int p0 = 0; p0 < g.n;) {
+    if (g.n - p0 > 16) {
+      gateup_pass<U, 2, kStream>(p, g, Iw, u0, p0, red);
+      p0 += 32;
+    } else {
+      gateup_pass<U, 1, kStream>(p, g, Iw, u0, p0, red);
+      p0 += 16;
+    }
+  }
+}
+
+template <int U, int NT, bool kStream, bool kVecB>
+__device__ __forceinline__ void down_pass(const F32Params& p, const Group& g, int Kd, int j0, int p0, f32x4* red) {
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, q = lane >> 4, c = lane & 15;
+  const int H = p.H;
+  const float* W = g.expert >= 0 ? p.w2 + static_cast<size_t>(g.expert) * H * p.I : p.ws2;
+  const int jc = min(j0 + U * c, H - U);
+  const float* const pw[1] = {W + 4 * static_cast<size_t>(q) * H + jc};
+  const float* pb[NT];
+#pragma unroll
+  for (int ct = 0; ct < NT; ++ct)
+    pb[ct] = p.hbuf + static_cast<size_t>(g.r0 + min(p0 + ct * 16 + c, g.n - 1)) * p.ldh + 4 * q;
+  const int ng = (Kd + kGroup - 1) / kGroup, per = (ng + kWaves - 1) / kWaves;
+  f32x4 acc[1][U][NT];
+  zero_f32(acc);
+  wave_dot_f32<U, 1, NT, kStream, kVecB>(pw, H, pb, kGroup, Kd, wave * per, min(ng, (wave + 1) * per), q, acc);
+  reduce_waves_f32(acc, red, wave, lane);
+  if (wave == 0) {
+#pragma unroll
+    for (int ct = 0; ct < NT; ++ct) {
+      const int col = p0 + ct * 16 + c;
+      if (col >= g.n) continue;
+      const int row = g.r0 + col;
+      float* dst = g.tok ? p.slot_out + (static_cast<size_t>(p.row_token[row]) * p.k + p.row_slot[row]) * H
+                         : p.shared_out + static_cast<size_t>(g.t0 + col) * H;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int j1 = j0 + U * (4 * q + r);
+        if constexpr (U == 4) {
+          if (j1 < H)
+            *reinterpret_cast<f32x4*>(dst + j1) =
+                f32x4{acc[0][0][ct][r], acc[0][1][ct][r], acc[0][2][ct][r], acc[0][3][ct][r]};  // H % 4 == 0
+        } else {
+          if (j1 < H) dst[j1] = acc[0][0][ct][r];
+        }
+      }
+    }
+  }
+  __syncthreads();
+}
+
+// grid (ceil(H / (16 U)), items): output features 16*U*bx .. of item y.
+// kVecB: rows of the activations are 16-byte aligned (ldh % 4 == 0).
+template <int U, bool kStream, bool kVecB>
+__global__ __launch_bounds__(kThreads, 2) void ffn_down_f32_kernel(F32Params p) {
+  __shared__ f32x4 red[(kWaves - 1) * U * 2 * kWave];
+  Group g;
+  if (!decode_item(blockIdx.y, 0, p.max_work, p.n_work, p.work, p.row_token, p.T, p.Tk, p.E, g)) return;
+  const int Kd = g.expert >= 0 ? p.I : p.I_s;
+  const int j0 = blockIdx.x * 16 * U;
+  for (int p0 = 0; p0 < g.n;) {
+    if (g.n - p0 > 16) {
+      down_pass<U, 2, kStream, kVecB>(p, g, Kd, j0, p0, red);
+      p0 += 32;
+    } else {
+      down_pass<U, 1, kStream, kVecB>(p, g, Kd, j0, p0, red);
+      p0 += 16;
+    }
+  }
+}
+
+// Workgroups below which the launch is spread finer (16 instead of 64 units
+// per workgroup): one per CU.
+constexpr long kFillGroups = 256;
+
+}  // namespace
+
+hipError_t launch_ffn_f32(const FfnArgs& a, int ldh, int items, hipStream_t s) {
+  F32Params p{static_cast<const float*>(a.x), static_cast<const float*>(a.w13), static_cast<const float*>(a.w2),
+              static_cast<const float*>(a.ws13), static_cast<const float*>(a.ws2), a.sched.n_work, a.sched.work,
+              a.sched.row_token, a.sched.row_slot, a.T, a.H, a.E, a.I, a.I_s, a.k, a.T * a.k, a.max_work, ldh,
+              static_cast<float*>(a.workspace), static_cast<float*>(a.slot_out), a.shared_out};
+  // Items of few rows read their weights once per launch: non-temporal loads.
+  const long rows = static_cast<long>(a.T) * std::max(a.k, 1);
+  const bool stream = rows <= 32L * items;
+  const bool wide_ok = a.I % 4 == 0 && a.I_s % 4 == 0;
+  const bool wide = wide_ok && static_cast<long>((ldh + 63) / 64) * items >= kFillGroups;
+  const dim3 g_gu((ldh + (wide ? 63 : 15)) / (wide ? 64 : 16), items);
+  if (wide) {
+    if (stream)
+      ffn_gateup_f32_kernel<4, true><<<g_gu, kThreads, 0, s>>>(p);
+    else
+      ffn_gateup_f32_kernel<4, false><<<g_gu, kThreads, 0, s>>>(p);
+  } else {
+    if (stream)
+      ffn_gateup_f32_kernel<1, true><<<g_gu, kThreads, 0, s>>>(p);
+    else
+      ffn_gateup_f32_kernel<1, false><<<g_gu, kThreads, 0, s>>>(p);
+  }
+  hipError_t err = hipGetLastError();
+  if (err != hipSuccess) return err;
+  const bool vec_b = ldh % 4 == 0;
+  const bool wide_dn = static_cast<long>((a.H + 63) / 64) * items >= kFillGroups;
+  const dim3 g_dn((a.H + (wide_dn ? 63 : 15)) / (wide_dn ? 64 : 16), items);
+#define DMOE_DOWN_F32(U_, S_, V_)                                 \
+  if (wide_dn == (U_ == 4) && stream == S_ && vec_b == V_) \
+    ffn_down_f32_kernel<U_, S_, V_><<<g_dn, kThreads, 0, s>>>(p);
+  DMOE_DOWN_F32(4, true, true)
+  DMOE_DOWN_F32(4, false, true)
+  DMOE_DOWN_F32(1, true, true)
+  DMOE_DOWN_F32(1, false, true)
+  DMOE_DOWN_F32(4, true, false)
+  DMOE_DOWN_F32(4, false, false)
+  DMOE_DOWN_F32(1, true, false)
+  DMOE_DOWN_F32(1, false, false)
+#undef DMOE_DOWN_F32
+  return hipGetLastError();
+}
+
+}  // namespace dmoe

@@ -198,7 +198,7 @@ static bool route_block_fits(int gs, int E, int k, bool block) {
 static hipError_t launch_route_topp(const RouteArgs& a, dmoe_dtype dt, hipStream_t s) {
   hipError_t err;
   bool own_done = false;
-  if (dt == DMOE_BF16 && softmax_token_topk_fits(a.E)) {
+  if (softmax_token_topk_fits(a.E)) {
     float* part = nullptr;
     int S = 1;
     err = launch_router_partials(a.x, a.w, dt, a.T, a.H, a.E, a.probs, a.x_chunked, a.workspace, a.ws_bytes, s,
@@ -258,7 +258,7 @@ hipError_t launch_route(const RouteArgs& a, dmoe_dtype dt, hipStream_t s) {
     return launch_schedule(a.experts, G, a.gs, a.k, a.E, a.sched, s);
   }
   hipError_t err;
-  if (!a.block && dt == DMOE_BF16 && softmax_token_topk_fits(a.E)) {
+  if (!a.block && softmax_token_topk_fits(a.E)) {
     // token routing: the softmax and each token's selection in one launch
     float* part = nullptr;
     int S = 1;

@@ -10,7 +10,7 @@
 // workgroups so that more CUs share the router matrix; the S partial logits
 // go to the workspace and the softmax sums them in slice order, so the result
 // does not depend on scheduling.
-// f32: one thread per (token, expert) dot product.
+// f32: 16 x 16 tiles on the fp32 matrix cores, the waves splitting H.
 // Softmax: one wave per token row; all partial loads of a pass are issued
 // together and the row is staged in LDS (one read pass, one write pass).
 // Optionally the kernel also stores x in the chunk-major layout the expert
@@ -254,27 +254,75 @@ __global__ __launch_bounds__(256) void router_tile_bf16_kernel(
   }
 }
 
-// fp32 router: grid (ceil(E / 16), T).  Wave w of a workgroup computes the
-// logits of experts 16*bx + w, + 4, ... for token t: each lane accumulates
-// the features h = lane, lane + 64, ... of x[t] . w[e] (coalesced row reads),
-// then the wave sums its lanes in a fixed order (dev::wave_sum).
-constexpr int kF32RouterExperts = 16;
+// fp32 router on the fp32 matrix cores (v_mfma_f32_16x16x4_f32: fp32
+// operands and sums): grid (ceil(T / 16), ceil(E / 16)), a 16-token x
+// 16-expert tile per workgroup.  The eight waves split the hidden dimension in
+// groups of 16 features (lane (q, c) of a group holds features 4q .. 4q+3 of
+// its token and of its expert, one 16-byte load each), up to kF32Burst groups
+// in flight, and the partial tiles are summed in wave order.  What bounds it
+// is one memory round trip: a wave per (token, 4 experts) with a 64-lane
+// reduction per dot product, which it replaces, took 25 us for 64 tokens x 32
+// experts at hidden 1024.  kVec: rows are 16-byte aligned (H % 4 == 0); a
+// last group past H is masked in both operands.
+constexpr int kF32RouterWaves = 8;
+constexpr int kF32Burst = 8;
 
-__global__ __launch_bounds__(256) void router_logits_f32_kernel(
+template <bool kVec>
+__global__ __launch_bounds__(kF32RouterWaves * kWave) void router_logits_f32_kernel(
     const float* __restrict__ x, const float* __restrict__ w, int T, int H, int E,
     float* __restrict__ part, float* __restrict__ xk) {
-  const int t = blockIdx.y;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const float* xr = x + static_cast<size_t>(t) * H;
-  if (xk && blockIdx.x == 0)
-    for (int h = threadIdx.x; h < H; h += blockDim.x) xk[(static_cast<size_t>(h >> 2) * T + t) * 4 + (h & 3)] = xr[h];
-  const int e1 = min(E, static_cast<int>(blockIdx.x + 1) * kF32RouterExperts);
-  for (int e = blockIdx.x * kF32RouterExperts + wave; e < e1; e += 4) {
-    const float* wr = w + static_cast<size_t>(e) * H;
-    float acc = 0.f;
-    for (int h = lane; h < H; h += kWave) acc = fmaf(xr[h], wr[h], acc);
-    acc = dev::wave_sum(acc);
-    if (lane == 0) part[static_cast<size_t>(t) * E + e] = acc;
+  __shared__ f32x4 red[kF32RouterWaves - 1][kWave];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, q = lane >> 4, c = lane & 15;
+  const int t0 = blockIdx.x * 16, e0 = blockIdx.y * 16;
+  // ragged token / expert tails: clamp the rows read, skip the writes
+  const float* px = x + static_cast<size_t>(min(t0 + c, T - 1)) * H + 4 * q;
+  const float* pw = w + static_cast<size_t>(min(e0 + c, E - 1)) * H + 4 * q;
+  const int ng = (H + 15) / 16, per = (ng + kF32RouterWaves - 1) / kF32RouterWaves;
+  const int g0 = wave * per, g1 = min(ng, g0 + per);
+  const bool write_x = xk && blockIdx.y == 0 && t0 + c < T;  // x_chunked needs H % 4 == 0
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  for (int gb = g0; gb < g1; gb += kF32Burst) {
+    f32x4 a[kF32Burst], b[kF32Burst];
+#pragma unroll
+    for (int s = 0; s < kF32Burst; ++s) {
+      const int g = min(gb + s, g1 - 1);
+      if constexpr (kVec) {
+        // a lane's four features lie wholly in or past the row
+        const int off = min(16 * g, H - 4 - 4 * q);
+        a[s] = *reinterpret_cast<const f32x4*>(px + off);
+        b[s] = *reinterpret_cast<const f32x4*>(pw + off);
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int off = min(16 * g + i, H - 1 - 4 * q);
+          a[s][i] = 16 * g + 4 * q + i < H ? px[off] : 0.f;
+          b[s][i] = 16 * g + 4 * q + i < H ? pw[off] : 0.f;
+        }
+      }
+    }
+#pragma unroll
+    for (int s = 0; s < kF32Burst; ++s) {
+      const int g = gb + s;
+      if (g >= g1) break;  // uniform
+      const bool in = !kVec || 16 * g + 4 * q < H;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(in ? a[s][i] : 0.f, in ? b[s][i] : 0.f, acc, 0, 0, 0);
+      if (kVec && write_x && in)
+        *reinterpret_cast<f32x4*>(xk + (static_cast<size_t>(4 * g + q) * T + t0 + c) * 4) = a[s];
+    }
+  }
+  if (wave > 0) red[wave - 1][lane] = acc;
+  __syncthreads();
+  if (wave != 0) return;
+#pragma unroll
+  for (int ww = 0; ww < kF32RouterWaves - 1; ++ww) acc += red[ww][lane];
+  const int e = e0 + c;
+  if (e >= E) return;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int t = t0 + 4 * q + r;
+    if (t < T) part[static_cast<size_t>(t) * E + e] = acc[r];
   }
 }
 
@@ -396,10 +444,14 @@ hipError_t launch_router_partials(const void* x, const void* w, dmoe_dtype dt, i
       router_logits_bf16_kernel<<<grid, 256, 0, s>>>(xb, wb, T, H, E, S, part, xkb);
     }
   } else {
-    dim3 grid((E + kF32RouterExperts - 1) / kF32RouterExperts, T);
-    router_logits_f32_kernel<<<grid, 256, 0, s>>>(static_cast<const float*>(x),
-                                                   static_cast<const float*>(w), T, H, E, part,
-                                                   static_cast<float*>(x_chunked));
+    const dim3 grid((T + 15) / 16, (E + 15) / 16);
+    const float* xf = static_cast<const float*>(x);
+    const float* wf = static_cast<const float*>(w);
+    float* xkf = static_cast<float*>(x_chunked);
+    if (H % 4 == 0)
+      router_logits_f32_kernel<true><<<grid, kF32RouterWaves * kWave, 0, s>>>(xf, wf, T, H, E, part, xkf);
+    else
+      router_logits_f32_kernel<false><<<grid, kF32RouterWaves * kWave, 0, s>>>(xf, wf, T, H, E, part, xkf);
   }
   *part_out = part;
   *S_out = S;
