@@ -12,14 +12,17 @@
 // values.  The order in which a matrix instruction sums its indices does not
 // matter as long as both operands agree, so neither is rearranged.
 //
-// What bounds it: the weight stream.  A forward of few tokens reads each
-// selected expert's weights once; a workgroup covers 16*U units, its four
-// waves split the reduction (summed in wave order through LDS, so results do
-// not depend on scheduling) and keep two bursts of weights in flight each.
-// The scalar-FMA kernels this replaces kept eight tokens per pass, one
-// dependent chain of loads per pass: two blocks of 32 tokens over 32 experts
-// (hidden 1024, intermediate 512, top-4, token routing) took 344 + 122 us for
-// gate/up + down, 207 MB at 0.45 TB/s.
+// What bounds it: the weight stream at few tokens, the fp32 matrix rate
+// (a sixteenth of bf16's) at many.  A workgroup covers 16*U units and at most
+// 32 rows of an item (its other rows are further workgroups: at this rate a
+// second pass costs more than reading the weights again from a cache); its
+// four waves split the reduction (summed in wave order through LDS, so
+// results do not depend on scheduling) and keep two bursts of weights in
+// flight each.  Measured on two blocks of 32 tokens over 32 experts (hidden
+// 1024, intermediate 512 + shared 512, top-4, token routing; 207 MB), whole
+// layer: 513 us with scalar-FMA kernels of eight tokens per pass, 137 with
+// these at U = 4 and passes in a loop (the U = 4 gate/up spilled), 100 at
+// U = 2, 80 with the passes spread over workgroups.
 #include <algorithm>
 
 #include "dmoe_common.h"
@@ -33,11 +36,13 @@ using fdev::Group;
 
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / kWave;
+constexpr int kPassRows = 32;  // rows of an item per workgroup (two token tiles)
 constexpr int kGroup = 16;  // reduction indices of one group: four per 16-lane row
-constexpr int kBurst = 2;   // groups loaded together; two bursts are in flight
+constexpr int kBurst = 2;  // groups loaded together; two such bursts are in flight
 
 struct F32Params {
   const float* xk;  // activations, chunk-major [H/4][T][4]
+  const float* xr;  // the same row-major [T][H], or nullptr
   const float *w13, *w2, *ws13, *ws2;
   const int *n_work, *work, *row_token, *row_slot;
   int T, H, E, I, I_s, k, Tk, max_work, ldh;
@@ -56,11 +61,12 @@ struct Burst {
 
 template <int U, bool kStream>
 __device__ __forceinline__ void ld_units(const float* p, float (&v)[U]) {
-  if constexpr (U == 4) {
-    const f32x4* p4 = reinterpret_cast<const f32x4*>(p);
-    const f32x4 x = kStream ? __builtin_nontemporal_load(p4) : *p4;
+  if constexpr (U > 1) {
+    typedef float vec __attribute__((ext_vector_type(U)));
+    const vec* pv = reinterpret_cast<const vec*>(p);
+    const vec x = kStream ? __builtin_nontemporal_load(pv) : *pv;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) v[u] = x[u];
+    for (int u = 0; u < U; ++u) v[u] = x[u];
   } else {
     static_assert(U == 1, "units per lane");
     v[0] = kStream ? __builtin_nontemporal_load(p) : *p;
@@ -81,14 +87,15 @@ __device__ __forceinline__ void mma_group(const float (&a)[4][NM][U], const f32x
 }
 
 // acc += W . B over the reduction groups g0 .. g1-1 of a reduction of length
-// K.  pw[m]: matrix m at this lane's units, index 4*q; row stride ldw.
+// K.  W[m]: matrix m, row stride ldw; lo: this lane's offset in it, index 4*q
+// at its units.
 // pb[ct]: token tile ct's values at index 4*q; bstep elements to the next
 // group; kVecB: its four values are one aligned 16-byte load.  Groups past
 // the end of a burst reload the last one (straight-line loads) and are not
 // used; a last group that K does not fill is loaded element by element, with
 // zeros past K in both operands.
 template <int U, int NM, int NT, bool kStream, bool kVecB>
-__device__ __forceinline__ void wave_dot_f32(const float* const (&pw)[NM], size_t ldw, const float* const (&pb)[NT],
+__device__ __forceinline__ void wave_dot_f32(const float* const (&W)[NM], uint32_t lo, size_t ldw, const float* const (&pb)[NT],
                                              int bstep, int K, int g0, int g1, int q, f32x4 (&acc)[NM][U][NT]) {
   const int nfull = K / kGroup;
   const int ge = min(g1, nfull);
@@ -110,7 +117,7 @@ __device__ __forceinline__ void wave_dot_f32(const float* const (&pw)[NM], size_
 #pragma unroll
       for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int m = 0; m < NM; ++m) ld_units<U, kStream>(pw[m] + (row + i) * ldw, d.a[s][i][m]);
+        for (int m = 0; m < NM; ++m) ld_units<U, kStream>(W[m] + (row + i) * ldw + lo, d.a[s][i][m]);
     }
   };
   auto mma = [&](const Burst<U, NM, NT>& d, int g) {
@@ -141,7 +148,7 @@ __device__ __forceinline__ void wave_dot_f32(const float* const (&pw)[NM], size_
 #pragma unroll
       for (int m = 0; m < NM; ++m) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) a[i][m][u] = in ? pw[m][(row + i) * ldw + u] : 0.f;
+        for (int u = 0; u < U; ++u) a[i][m][u] = in ? (W[m] + (row + i) * ldw)[lo + u] : 0.f;
       }
 #pragma unroll
       for (int ct = 0; ct < NT; ++ct) b[ct][i] = in ? pb[ct][static_cast<size_t>(nfull) * bstep + i] : 0.f;
@@ -188,22 +195,24 @@ __device__ __forceinline__ void zero_f32(f32x4 (&acc)[NM][U][NT]) {
 // One pass of the gate/up kernel: 16*NT rows of the item from row p0.
 template <int U, int NT, bool kStream>
 __device__ __forceinline__ void gateup_pass(const F32Params& p, const Group& g, int Iw, int u0, int p0, f32x4* red) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, q = lane >> 4, c = lane & 15;
+  const int wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, q = lane >> 4, c = lane & 15;
   const float* W = g.expert >= 0 ? p.w13 + static_cast<size_t>(g.expert) * 2 * p.I * p.H : p.ws13;
   const size_t ldw = 2 * static_cast<size_t>(Iw);
   const int uc = min(u0 + U * c, Iw - U);  // units past the last: the last ones again, not stored
-  const float* const pw[2] = {W + 4 * q * ldw + uc, W + 4 * q * ldw + Iw + uc};
+  const float* const pw[2] = {W, W + Iw};
+  const uint32_t lo = 4 * q * static_cast<uint32_t>(ldw) + uc;
   const float* pb[NT];
 #pragma unroll
   for (int ct = 0; ct < NT; ++ct) {
     const int col = min(p0 + ct * 16 + c, g.n - 1);
     const int tok = g.tok ? g.tok[col] : g.t0 + col;
-    pb[ct] = p.xk + (static_cast<size_t>(q) * p.T + tok) * 4;
+    pb[ct] = p.xr ? p.xr + static_cast<size_t>(tok) * p.H + 4 * q : p.xk + (static_cast<size_t>(q) * p.T + tok) * 4;
   }
   const int ng = (p.H + kGroup - 1) / kGroup, per = (ng + kWaves - 1) / kWaves;
   f32x4 acc[2][U][NT];
   zero_f32(acc);
-  wave_dot_f32<U, 2, NT, kStream, true>(pw, ldw, pb, 16 * p.T, p.H, wave * per, min(ng, (wave + 1) * per), q, acc);
+  wave_dot_f32<U, 2, NT, kStream, true>(pw, lo, ldw, pb, p.xr ? kGroup : kGroup * p.T, p.H, wave * per, min(ng, (wave + 1) * per), q, acc);
   reduce_waves_f32(acc, red, wave, lane);
   if (wave == 0) {
     // accumulator r of lane (q, c): units u0 + U*(4q + r) + u of row p0 + 16ct + c
@@ -218,19 +227,24 @@ __device__ __forceinline__ void gateup_pass(const F32Params& p, const Group& g, 
         float h[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) h[u] = silu_f32(acc[0][u][ct][r]) * acc[1][u][ct][r];
-        if constexpr (U == 4) {
-          if (u1 < Iw) *reinterpret_cast<f32x4*>(dst + u1) = f32x4{h[0], h[1], h[2], h[3]};  // I % 4 == 0
-        } else {
-          if (u1 < Iw) dst[u1] = h[0];
+        if (u1 < Iw) {  // I % U == 0: the U units lie wholly in or past the row
+          if constexpr (U > 1) {
+            typedef float vec __attribute__((ext_vector_type(U)));
+            vec v;
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = h[u];
+            *reinterpret_cast<vec*>(dst + u1) = v;
+          } else {
+            dst[u1] = h[0];
+          }
         }
       }
     }
   }
-  __syncthreads();  // red is reused by the next pass
 }
 
-// grid (ceil(ldh / (16 U)), items): units 16*U*bx .. of item y.  U = 4 needs
-// I % 4 == 0 and I_s % 4 == 0 (aligned 16-byte loads and stores).
+// grid (ceil(ldh / (16 U)), items, passes): units 16*U*bx .. of rows 32*bz ..
+// of item y.  I % U == 0 and I_s % U == 0 (aligned loads and stores).
 template <int U, bool kStream>
 __global__ __launch_bounds__(kThreads, 2) void ffn_gateup_f32_kernel(F32Params p) {
   __shared__ f32x4 red[(kWaves - 1) * 2 * U * 2 * kWave];
@@ -239,24 +253,23 @@ __global__ __launch_bounds__(kThreads, 2) void ffn_gateup_f32_kernel(F32Params p
   const int Iw = g.expert >= 0 ? p.I : p.I_s;
   const int u0 = blockIdx.x * 16 * U;
   if (u0 >= Iw) return;
-  for (int p0 = 0; p0 < g.n;) {
-    if (g.n - p0 > 16) {
-      gateup_pass<U, 2, kStream>(p, g, Iw, u0, p0, red);
-      p0 += 32;
-    } else {
-      gateup_pass<U, 1, kStream>(p, g, Iw, u0, p0, red);
-      p0 += 16;
-    }
-  }
+  const int p0 = blockIdx.z * kPassRows;
+  if (p0 >= g.n) return;
+  if (g.n - p0 > 16)
+    gateup_pass<U, 2, kStream>(p, g, Iw, u0, p0, red);
+  else
+    gateup_pass<U, 1, kStream>(p, g, Iw, u0, p0, red);
 }
 
 template <int U, int NT, bool kStream, bool kVecB>
 __device__ __forceinline__ void down_pass(const F32Params& p, const Group& g, int Kd, int j0, int p0, f32x4* red) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, q = lane >> 4, c = lane & 15;
+  const int wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, q = lane >> 4, c = lane & 15;
   const int H = p.H;
   const float* W = g.expert >= 0 ? p.w2 + static_cast<size_t>(g.expert) * H * p.I : p.ws2;
   const int jc = min(j0 + U * c, H - U);
-  const float* const pw[1] = {W + 4 * static_cast<size_t>(q) * H + jc};
+  const float* const pw[1] = {W};
+  const uint32_t lo = 4 * q * static_cast<uint32_t>(H) + jc;
   const float* pb[NT];
 #pragma unroll
   for (int ct = 0; ct < NT; ++ct)
@@ -264,7 +277,7 @@ __device__ __forceinline__ void down_pass(const F32Params& p, const Group& g, in
   const int ng = (Kd + kGroup - 1) / kGroup, per = (ng + kWaves - 1) / kWaves;
   f32x4 acc[1][U][NT];
   zero_f32(acc);
-  wave_dot_f32<U, 1, NT, kStream, kVecB>(pw, H, pb, kGroup, Kd, wave * per, min(ng, (wave + 1) * per), q, acc);
+  wave_dot_f32<U, 1, NT, kStream, kVecB>(pw, lo, H, pb, kGroup, Kd, wave * per, min(ng, (wave + 1) * per), q, acc);
   reduce_waves_f32(acc, red, wave, lane);
   if (wave == 0) {
 #pragma unroll
@@ -287,10 +300,9 @@ __device__ __forceinline__ void down_pass(const F32Params& p, const Group& g, in
       }
     }
   }
-  __syncthreads();
 }
 
-// grid (ceil(H / (16 U)), items): output features 16*U*bx .. of item y.
+// grid (ceil(H / (16 U)), items, passes): output features 16*U*bx .. of item y.
 // kVecB: rows of the activations are 16-byte aligned (ldh % 4 == 0).
 template <int U, bool kStream, bool kVecB>
 __global__ __launch_bounds__(kThreads, 2) void ffn_down_f32_kernel(F32Params p) {
@@ -299,39 +311,43 @@ __global__ __launch_bounds__(kThreads, 2) void ffn_down_f32_kernel(F32Params p) 
   if (!decode_item(blockIdx.y, 0, p.max_work, p.n_work, p.work, p.row_token, p.T, p.Tk, p.E, g)) return;
   const int Kd = g.expert >= 0 ? p.I : p.I_s;
   const int j0 = blockIdx.x * 16 * U;
-  for (int p0 = 0; p0 < g.n;) {
-    if (g.n - p0 > 16) {
-      down_pass<U, 2, kStream, kVecB>(p, g, Kd, j0, p0, red);
-      p0 += 32;
-    } else {
-      down_pass<U, 1, kStream, kVecB>(p, g, Kd, j0, p0, red);
-      p0 += 16;
-    }
-  }
+  const int p0 = blockIdx.z * kPassRows;
+  if (p0 >= g.n) return;
+  if (g.n - p0 > 16)
+    down_pass<U, 2, kStream, kVecB>(p, g, Kd, j0, p0, red);
+  else
+    down_pass<U, 1, kStream, kVecB>(p, g, Kd, j0, p0, red);
 }
 
-// Workgroups below which the launch is spread finer (16 instead of 64 units
-// per workgroup): one per CU.
+// Units per lane: gate/up 2 (two matrices; at 4 the operands leave one burst
+// in flight, 80 -> 86 us on the layer above), down 4; launches of fewer than
+// kFillGroups workgroups (one per CU) take 1, four times the workgroups (a
+// tiny layer of hidden 256, intermediate 128, 8 tokens: gate/up 4.8 us).
+constexpr int kWideGu = 2, kWideDn = 4;
 constexpr long kFillGroups = 256;
+
 
 }  // namespace
 
 hipError_t launch_ffn_f32(const FfnArgs& a, int ldh, int items, hipStream_t s) {
-  F32Params p{static_cast<const float*>(a.x), static_cast<const float*>(a.w13), static_cast<const float*>(a.w2),
+  F32Params p{static_cast<const float*>(a.x), static_cast<const float*>(a.xr), static_cast<const float*>(a.w13), static_cast<const float*>(a.w2),
               static_cast<const float*>(a.ws13), static_cast<const float*>(a.ws2), a.sched.n_work, a.sched.work,
               a.sched.row_token, a.sched.row_slot, a.T, a.H, a.E, a.I, a.I_s, a.k, a.T * a.k, a.max_work, ldh,
               static_cast<float*>(a.workspace), static_cast<float*>(a.slot_out), a.shared_out};
   // Items of few rows read their weights once per launch: non-temporal loads.
   const long rows = static_cast<long>(a.T) * std::max(a.k, 1);
   const bool stream = rows <= 32L * items;
-  const bool wide_ok = a.I % 4 == 0 && a.I_s % 4 == 0;
-  const bool wide = wide_ok && static_cast<long>((ldh + 63) / 64) * items >= kFillGroups;
-  const dim3 g_gu((ldh + (wide ? 63 : 15)) / (wide ? 64 : 16), items);
+  const bool wide_ok = a.I % kWideGu == 0 && a.I_s % kWideGu == 0;  // aligned loads and stores
+  const bool wide = wide_ok && static_cast<long>((ldh + 16 * kWideGu - 1) / (16 * kWideGu)) * items >= kFillGroups;
+  // an item holds each token at most once
+  const int passes = (std::min(a.T, DMOE_WORK_ROWS) + kPassRows - 1) / kPassRows;
+  const int gu = wide ? 16 * kWideGu : 16;  // units per gate/up workgroup
+  const dim3 g_gu((ldh + gu - 1) / gu, items, passes);
   if (wide) {
     if (stream)
-      ffn_gateup_f32_kernel<4, true><<<g_gu, kThreads, 0, s>>>(p);
+      ffn_gateup_f32_kernel<kWideGu, true><<<g_gu, kThreads, 0, s>>>(p);
     else
-      ffn_gateup_f32_kernel<4, false><<<g_gu, kThreads, 0, s>>>(p);
+      ffn_gateup_f32_kernel<kWideGu, false><<<g_gu, kThreads, 0, s>>>(p);
   } else {
     if (stream)
       ffn_gateup_f32_kernel<1, true><<<g_gu, kThreads, 0, s>>>(p);
@@ -341,17 +357,18 @@ hipError_t launch_ffn_f32(const FfnArgs& a, int ldh, int items, hipStream_t s) {
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
   const bool vec_b = ldh % 4 == 0;
-  const bool wide_dn = static_cast<long>((a.H + 63) / 64) * items >= kFillGroups;
-  const dim3 g_dn((a.H + (wide_dn ? 63 : 15)) / (wide_dn ? 64 : 16), items);
+  const bool wide_dn = static_cast<long>((a.H + 16 * kWideDn - 1) / (16 * kWideDn)) * items >= kFillGroups;
+  const int du = wide_dn ? 16 * kWideDn : 16;
+  const dim3 g_dn((a.H + du - 1) / du, items, passes);
 #define DMOE_DOWN_F32(U_, S_, V_)                                 \
-  if (wide_dn == (U_ == 4) && stream == S_ && vec_b == V_) \
+  if (wide_dn == (U_ == kWideDn) && stream == S_ && vec_b == V_) \
     ffn_down_f32_kernel<U_, S_, V_><<<g_dn, kThreads, 0, s>>>(p);
-  DMOE_DOWN_F32(4, true, true)
-  DMOE_DOWN_F32(4, false, true)
+  DMOE_DOWN_F32(kWideDn, true, true)
+  DMOE_DOWN_F32(kWideDn, false, true)
   DMOE_DOWN_F32(1, true, true)
   DMOE_DOWN_F32(1, false, true)
-  DMOE_DOWN_F32(4, true, false)
-  DMOE_DOWN_F32(4, false, false)
+  DMOE_DOWN_F32(kWideDn, true, false)
+  DMOE_DOWN_F32(kWideDn, false, false)
   DMOE_DOWN_F32(1, true, false)
   DMOE_DOWN_F32(1, false, false)
 #undef DMOE_DOWN_F32
