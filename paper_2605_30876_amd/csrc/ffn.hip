@@ -289,35 +289,77 @@ __device__ __forceinline__ bool map_item(const FfnParams& p, int gx, int& item, 
 
 // ---- tile kernels: many tokens per work item --------------------------------
 //
-// A workgroup covers 4 * kRowTiles (one or two) 16-row weight tiles (wave w: packed tiles
-// kRowTiles * (4*bx + w) + m, m < kRowTiles, over the whole reduction) x up
-// to 128 tokens of one work item (8 token tiles).  The reduction runs in
-// stages of kStageSteps K-steps: the stage's token fragments are loaded from
-// global memory once per workgroup into a double-buffered LDS stage read by
-// all four waves, each fragment read once per wave and applied to the
-// wave's kRowTiles weight tiles, while each wave streams its own weight tiles
-// into registers two stages ahead (HBM latency spans more than one stage's
-// matrix work).  Accumulation order (K ascending) and the epilogues match the
+// A workgroup of kWaves waves covers kWaves * kRowTiles 16-row weight tiles
+// (wave w: packed tiles kRowTiles * (kWaves*bx + w) + m, m < kRowTiles, over the whole
+// reduction) x up to 128 tokens of one work item (8 token tiles).  The
+// reduction runs in stages of kSteps K-steps.  A stage's token fragments go
+// from global memory straight into LDS (no registers), two stages ahead into a ring of
+// three stage buffers that all waves read, each fragment read once per wave
+// and applied to the wave's kRowTiles weight tiles; each wave streams its own
+// weight tiles into registers, two stages ahead as well.  One wait count and
+// one barrier end a stage: everything but the loads issued in this stage has
+// arrived.  Accumulation order (K ascending) and the epilogues match the
 // decode kernels.
+//
+// What bounds it: what a CU can have in flight to L2 and HBM.  Counters at 64
+// blocks of 64 tokens (hidden 2048, 256 experts of intermediate 512; gate/up
+// 255 us): matrix cores busy 28 %, L2-to-CU 2.75 GB (about 45 GB/s per CU
+// at an average request latency of 550 cycles), HBM side 1.27 GB; reading the
+// LDS fragments one, two or three tiles ahead measured the same.  Token
+// fragments two stages ahead without registers, instead of one stage ahead
+// through registers: that layer 508 -> 490 us, 16 x 32 tokens 173 -> 164,
+// the Zipf-biased hidden-4096 layer 188 -> 182.  Scaled-half outputs stored
+// as whole rows (below): 490 -> 441, 164 -> 159, 182 -> 173.
 constexpr int kTileTok = 8;       // token tiles per workgroup (128 tokens)
-constexpr int kStageSteps = 2;    // K-steps per LDS stage (two: 32 KB of LDS, three workgroups per CU)
 static_assert(kTileTok * 16 == DMOE_WORK_ROWS, "a tile workgroup covers one work item's rows");
 
+// One stage's token fragments, each in the lane order of the matrix operand.
+template <int kSteps>
+using TokStage = bf16x8[kSteps][kTileTok][kWave];  // 8 KiB per step
+
+// LDS of a tile workgroup.  The three stage buffers are separate arrays so
+// that the compiler can tell the one being read from those being loaded: it
+// would otherwise wait for every load into LDS before each fragment read.
+template <int kWaves, int kSteps>
+struct TileLds {
+  TokStage<kSteps>&s0, &s1, &s2;
+  int* dst;     // [DMOE_WORK_ROWS] slot row of each row of the item (down projection)
+  int8_t* exps; // [DMOE_WORK_ROWS][2 * kWaves] exponents of the output tiles
+};
+
+// Wait until at most N vector-memory operations of this wave are outstanding.
+template <int N>
+__device__ __forceinline__ void wait_vm() {
+  __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
+}
+
+// 16 bytes per lane from global memory straight into LDS at dst + 16*lane
+// (dst uniform over the wave).
+__device__ __forceinline__ void dma16(const bf16_t* src, bf16x8* dst) {
+  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
+                                   (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
+}
+
 // The workgroup's work once its item is known (kStream: weights loaded
-// non-temporally).
-template <bool kGateUp, int kRowTiles, bool kStream>
+// non-temporally; kCt: token tiles the code covers, at least the item's).
+template <bool kGateUp, int kRowTiles, int kWaves, int kSteps, bool kStream, int kCt>
 __device__ __forceinline__ void tile_body(const FfnParams& p, const Group& g, int bx,
-                                          bf16x8 (&stage)[2][kStageSteps][kTileTok][kWave]) {
-  constexpr int kTileRows = 4 * kRowTiles;  // weight tiles per workgroup
+                                          const TileLds<kWaves, kSteps>& lds) {
+  constexpr int kTileRows = kWaves * kRowTiles;  // weight tiles per workgroup
+  // token fragments of a stage (tile, K-step) a wave loads
+  constexpr int kFrags = kSteps * kCt, kFragWave = (kFrags + kWaves - 1) / kWaves;
+  using Stage = TokStage<kSteps>;
   const int H = p.H;
   const int Iw = g.expert >= 0 ? p.I : p.I_s;
   const int Kd = kGateUp ? H : Iw;                    // reduction length
-  const int tiles = kGateUp ? Iw / 8 : H / 16;        // packed 16-row tiles of the matrix
+  const int tiles = kGateUp ? Iw / 8 : H / 16;        // packed 16-row tiles of the matrix (a multiple of 8)
   if (bx * kTileRows >= tiles) return;  // uniform: past the matrix
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  // tiles % kTileRows == 0 (H, I, I_s multiples of 128)
-  const int tile0 = (bx * 4 + wave) * kRowTiles;
-  const int ksteps = Kd >> 5;                         // multiple of kStageSteps
+  const int uw = __builtin_amdgcn_readfirstlane(wave);
+  // a wave past the matrix repeats the last tiles and stores nothing
+  const bool wave_live = (bx * kWaves + uw) * kRowTiles < tiles;
+  const int tile0 = min((bx * kWaves + wave) * kRowTiles, tiles - kRowTiles);
+  const int ksteps = Kd >> 5;                         // multiple of 4
   const bf16_t* W;
   if (kGateUp)
     W = g.expert >= 0 ? p.w13 + static_cast<size_t>(g.expert) * 2 * p.I * H : p.ws13;
@@ -325,151 +367,235 @@ __device__ __forceinline__ void tile_body(const FfnParams& p, const Group& g, in
     W = g.expert >= 0 ? p.w2 + static_cast<size_t>(g.expert) * H * p.I : p.ws2;
   const bf16_t* pa = W + static_cast<size_t>(tile0) * ksteps * kFrag + lane * 8;
   const size_t tstride = static_cast<size_t>(ksteps) * kFrag;  // next packed tile
-  const int nt = (g.n + 15) >> 4;  // live token tiles
 
-  // Token-fragment producer: thread t loads pieces (tile t/64, lane t%64) and
-  // (tile t/64 + 4, same lane) of every K-step of a stage.  Tiles past the
-  // item's last token load its last row again (straight-line code; those
-  // fragments are never used).
-  const int tid = threadIdx.x;
-  const int pl = tid & 63, pq = pl >> 4, pc = pl & 15;
-  const int pct = __builtin_amdgcn_readfirstlane(tid >> 6);  // the wave (uniform)
+  // Token-fragment producer: fragment f = step * kCt + tile of a stage is
+  // loaded by wave f % kWaves.  Tiles past the item's last token load its
+  // last row again (straight-line code; those fragments are never stored).
+  const int q = lane >> 4, c = lane & 15;
   const int rows_b = kGateUp ? p.T : p.R;  // rows of the chunk-major source
   const bf16_t* src = kGateUp ? p.xk : p.hk;
-  const bf16_t* pb[2];
-  int row[2];
+  const bf16_t* pb[kFragWave];
+  int row[kFragWave];
   bool gathered = false;
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int ct = pct + 4 * h;
-    const int col = min(ct * 16 + pc, g.n - 1);
+  for (int i = 0; i < kFragWave; ++i) {
+    const int col = min((uw + kWaves * i) % kCt * 16 + c, g.n - 1);
     if (kGateUp) {
-      row[h] = g.tok ? g.tok[col] : g.t0 + col;
-      if (p.xr && g.tok) gathered |= tile_gathered(row[h]);
+      row[i] = g.tok ? g.tok[col] : g.t0 + col;
+      if (p.xr && g.tok) gathered |= tile_gathered(row[i]);
     } else {
-      row[h] = g.r0 + col;
+      row[i] = g.r0 + col;
     }
   }
-#pragma unroll
-  for (int h = 0; h < 2; ++h)
-    pb[h] = gathered ? p.xr + static_cast<size_t>(row[h]) * H + pq * 8
-                     : src + (static_cast<size_t>(pq) * rows_b + row[h]) * 8;
   const int bstep = gathered ? 32 : 32 * rows_b;
+#pragma unroll
+  for (int i = 0; i < kFragWave; ++i)
+    pb[i] = (gathered ? p.xr + static_cast<size_t>(row[i]) * H + q * 8
+                      : src + (static_cast<size_t>(q) * rows_b + row[i]) * 8) +
+            (uw + kWaves * i) / kCt * bstep;
+  if (!kGateUp && g.tok && static_cast<int>(threadIdx.x) < g.n)  // read in the epilogue
+    lds.dst[threadIdx.x] = p.row_token[g.r0 + threadIdx.x] * p.k + p.row_slot[g.r0 + threadIdx.x];
 
-  f32x4 acc[kRowTiles][kTileTok];
+  f32x4 acc[kRowTiles][kCt];
 #pragma unroll
   for (int m = 0; m < kRowTiles; ++m)
 #pragma unroll
-    for (int ct = 0; ct < kTileTok; ++ct) acc[m][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // Weights (from HBM) run two stages ahead in a three-slot register ring,
-  // token fragments (mostly from L2) one stage ahead through registers into
-  // the LDS double buffer.  Loads are issued tokens first, then weights, so
-  // waiting for the next stage's tokens never waits for the newest weights.
-  bf16x8 a_reg[3][kStageSteps][kRowTiles], b_nxt[kStageSteps][2];
+    for (int ct = 0; ct < kCt; ++ct) acc[m][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+  bf16x8 a_reg[3][kSteps][kRowTiles];
+  const int nstages = ksteps / kSteps;  // at least two
 
-  auto load_a = [&](int st, bf16x8 (&a)[kStageSteps][kRowTiles]) {
+  auto load_a = [&](int st, bf16x8 (&a)[kSteps][kRowTiles]) {
 #pragma unroll
-    for (int s = 0; s < kStageSteps; ++s)
+    for (int s = 0; s < kSteps; ++s)
 #pragma unroll
       for (int m = 0; m < kRowTiles; ++m)
-        a[s][m] = kStream ? ld_bf16x8_stream(pa + m * tstride + (st * kStageSteps + s) * kFrag)
-                          : ld_bf16x8(pa + m * tstride + (st * kStageSteps + s) * kFrag);
+        a[s][m] = kStream ? ld_bf16x8_stream(pa + m * tstride + (st * kSteps + s) * kFrag)
+                          : ld_bf16x8(pa + m * tstride + (st * kSteps + s) * kFrag);
   };
-  auto load_b = [&](int st) {
+  auto load_b = [&](int st, Stage& d) {
 #pragma unroll
-    for (int s = 0; s < kStageSteps; ++s)
-#pragma unroll
-      for (int h = 0; h < 2; ++h) b_nxt[s][h] = ld_bf16x8(pb[h] + (st * kStageSteps + s) * bstep);
+    for (int i = 0; i < kFragWave; ++i) {
+      const int f = uw + kWaves * i;
+      if (kFrags % kWaves == 0 || f < kFrags) dma16(pb[i] + st * kSteps * bstep, &d[f / kCt][f % kCt][0]);
+    }
   };
-  auto store_b = [&](int buf) {
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-      if (pct + 4 * h < nt)  // uniform: the wave's tile holds tokens
-#pragma unroll
-        for (int s = 0; s < kStageSteps; ++s) stage[buf][s][pct + 4 * h][pl] = b_nxt[s][h];
-  };
+  // memory operations of one stage's loads; a wave that has a fragment less
+  // to load only waits for that much less of its own weights
+  constexpr int kIssued = kFragWave + kSteps * kRowTiles;
 
-  const int nstages = ksteps / kStageSteps;
-  load_b(0);
+  load_b(0, lds.s0);
   load_a(0, a_reg[0]);
-  if (nstages > 1) load_a(1, a_reg[1]);
-  store_b(0);
-  __syncthreads();
-  // stage st uses ring slot R = st % 3 (a compile-time index: the loop runs
-  // three stages per trip)
-  auto run_stage = [&](auto slot, int st) {
+  __builtin_amdgcn_sched_barrier(0);
+  load_b(1, lds.s1);
+  load_a(1, a_reg[1]);
+  __builtin_amdgcn_sched_barrier(0);
+  wait_vm<kIssued>();
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_sched_barrier(0);
+  // stage st uses ring slot and LDS buffer R = st % 3 (compile-time indexes:
+  // three stages per trip).  The buffer it refills was last read in stage
+  // st - 1, before the barrier that ended it.
+  auto run_stage = [&](auto slot, int st, Stage& cur, Stage& fill) {
     constexpr int R = decltype(slot)::value;
-    const bool more = st + 1 < nstages;
-    if (more) load_b(st + 1);
-    __builtin_amdgcn_sched_barrier(0);  // tokens before weights
-    if (st + 2 < nstages) load_a(st + 2, a_reg[(R + 2) % 3]);
+    const int nx = min(st + 2, nstages - 1);  // past the end: the last stage again, never used
+    load_b(nx, fill);
+    load_a(nx, a_reg[(R + 2) % 3]);
     __builtin_amdgcn_sched_barrier(0);
-    const int buf = st & 1;
-    // token tile by token tile over the item's nt live tiles: the next
-    // tile's fragments are read from LDS while this tile's matrix
-    // instructions run.  Each accumulator still sums K in order.
-    bf16x8 bc[kStageSteps], bn[kStageSteps];
+    // token tile by token tile: the next tile's fragments are read from LDS
+    // while this tile's matrix instructions run
+    bf16x8 b[2][kSteps];
 #pragma unroll
-    for (int s = 0; s < kStageSteps; ++s) bc[s] = stage[buf][s][0][lane];
+    for (int s = 0; s < kSteps; ++s) b[0][s] = cur[s][0][lane];
 #pragma unroll
-    for (int ct = 0; ct < kTileTok; ++ct) {
-      if (ct >= nt) break;  // uniform
-      if (ct + 1 < nt)
+    for (int ct = 0; ct < kCt; ++ct) {
+      if (ct + 1 < kCt) {
 #pragma unroll
-        for (int s = 0; s < kStageSteps; ++s) bn[s] = stage[buf][s][ct + 1][lane];
+        for (int s = 0; s < kSteps; ++s) b[(ct + 1) & 1][s] = cur[s][ct + 1][lane];
+      }
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int s = 0; s < kStageSteps; ++s)
+      for (int s = 0; s < kSteps; ++s)
 #pragma unroll
         for (int m = 0; m < kRowTiles; ++m)
-          acc[m][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a_reg[R][s][m], bc[s], acc[m][ct], 0, 0, 0);
-#pragma unroll
-      for (int s = 0; s < kStageSteps; ++s) bc[s] = bn[s];
+          acc[m][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a_reg[R][s][m], b[ct & 1][s], acc[m][ct], 0, 0, 0);
     }
-    if (more) store_b(buf ^ 1);
-    __syncthreads();
+    __builtin_amdgcn_sched_barrier(0);
+    wait_vm<kIssued>();  // all but this stage's loads: stage st + 1 has arrived
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
   };
-  for (int st = 0; st < nstages; st += 3) {
-    run_stage(std::integral_constant<int, 0>{}, st);
-    if (st + 1 < nstages) run_stage(std::integral_constant<int, 1>{}, st + 1);
-    if (st + 2 < nstages) run_stage(std::integral_constant<int, 2>{}, st + 2);
+  int st = 0;
+  for (; st + 3 <= nstages; st += 3) {
+    run_stage(std::integral_constant<int, 0>{}, st, lds.s0, lds.s2);
+    run_stage(std::integral_constant<int, 1>{}, st + 1, lds.s1, lds.s0);
+    run_stage(std::integral_constant<int, 2>{}, st + 2, lds.s2, lds.s1);
   }
+  if (st < nstages) run_stage(std::integral_constant<int, 0>{}, st, lds.s0, lds.s2);
+  if (st + 1 < nstages) run_stage(std::integral_constant<int, 1>{}, st + 1, lds.s1, lds.s0);
+  wait_vm<0>();  // the loads into LDS end before the buffers are reused or the workgroup ends
 
-  const int q = lane >> 4, c = lane & 15;
+  if constexpr (kGateUp) {
+    if (!wave_live) return;
 #pragma unroll
-  for (int m = 0; m < kRowTiles; ++m) {
-    const int tile = tile0 + m;
+    for (int m = 0; m < kRowTiles; ++m)
 #pragma unroll
-    for (int ct = 0; ct < kTileTok; ++ct) {
-      const int col = ct * 16 + c;
-      if (ct >= nt) continue;  // uniform
-      const f32x4 v = acc[m][ct];
-      const int ex = !kGateUp && g.tok ? slot_exponent(p, v) : 0;  // whole wave, before the row guard
-      if (col >= g.n) continue;
-      if (kGateUp) {
+      for (int ct = 0; ct < kCt; ++ct) {
+        const int col = ct * 16 + c;
+        if (col >= g.n) continue;
         // accumulators: (g_i, g_i+1, u_i, u_i+1) with i = 8*tile + 2q
+        const f32x4 v = acc[m][ct];
         const uint32_t h0 = f32_to_bf16(silu_f32(v[0]) * v[2]);
         const uint32_t h1 = f32_to_bf16(silu_f32(v[1]) * v[3]);
-        bf16_t* dst = p.hk + (static_cast<size_t>(tile) * p.R + g.r0 + col) * 8 + 2 * q;
+        bf16_t* dst = p.hk + (static_cast<size_t>(tile0 + m) * p.R + g.r0 + col) * 8 + 2 * q;
         *reinterpret_cast<uint32_t*>(dst) = h0 | (h1 << 16);
-      } else {
-        const int j = tile * 16 + 4 * q;
-        if (g.tok)
-          store_slot(p, g.r0 + col, j, v, ex);
-        else
-          *reinterpret_cast<f32x4*>(p.shared_out + static_cast<size_t>(g.t0 + col) * H + j) = v;
+      }
+    return;
+  }
+  if (!g.tok) {
+    if (!wave_live) return;
+#pragma unroll
+    for (int m = 0; m < kRowTiles; ++m)
+#pragma unroll
+      for (int ct = 0; ct < kCt; ++ct) {
+        const int col = ct * 16 + c;
+        if (col < g.n)
+          *reinterpret_cast<f32x4*>(p.shared_out + static_cast<size_t>(g.t0 + col) * H + (tile0 + m) * 16 + 4 * q) =
+              acc[m][ct];
+      }
+    return;
+  }
+  if (!p.slot_f16s) {
+    __syncthreads();  // lds.dst
+    if (!wave_live) return;
+#pragma unroll
+    for (int m = 0; m < kRowTiles; ++m)
+#pragma unroll
+      for (int ct = 0; ct < kCt; ++ct) {
+        const int col = ct * 16 + c;
+        if (col < g.n)
+          *reinterpret_cast<f32x4*>(static_cast<float*>(p.slot_out) + static_cast<size_t>(lds.dst[col]) * H +
+                                    (tile0 + m) * 16 + 4 * q) = acc[m][ct];
+      }
+    return;
+  }
+  // Scaled-half slot outputs go through LDS: a lane holds eight bytes of a
+  // row, and storing those directly makes four 32-byte write requests per
+  // row and tile pair where whole rows of the workgroup's features make two
+  // or four of 128 bytes (they were almost half of the kernel's L2 requests).
+  // A token tile is 16 rows of kRowBytes; 16-byte unit u of row c sits at u ^ c (no bank
+  // conflicts either way).  Rounds of kRound token tiles, as many as the
+  // three stage buffers hold.
+  constexpr int kRowBytes = kTileRows * 32;
+  constexpr int kPerBuf = static_cast<int>(sizeof(Stage)) / (16 * kRowBytes), kRound = 3 * kPerBuf;
+  static_assert(kPerBuf >= 1, "a stage buffer holds a token tile's outputs");
+  uint16_t* hv = static_cast<uint16_t*>(p.slot_out);
+  int8_t* ev = reinterpret_cast<int8_t*>(hv + static_cast<size_t>(p.T) * p.k * H);
+  constexpr int kUnits = kRowBytes / 16;                    // 16-byte units of a row
+  constexpr int kRowsPass = kWaves * kWave / kUnits;        // rows the workgroup stores together
+  const int units = min(kUnits, (tiles - bx * kTileRows) * 2);  // units of this workgroup's live tiles
+#pragma unroll
+  for (int c0 = 0; c0 < kCt; c0 += kRound) {
+    __syncthreads();  // the last stage (or round) has been read
+#pragma unroll
+    for (int ct = c0; ct < kCt && ct < c0 + kRound; ++ct) {
+      Stage& buf = (ct - c0) / kPerBuf == 0 ? lds.s0 : (ct - c0) / kPerBuf == 1 ? lds.s1 : lds.s2;
+      char* base = reinterpret_cast<char*>(&buf) + (ct - c0) % kPerBuf * 16 * kRowBytes;
+#pragma unroll
+      for (int m = 0; m < kRowTiles; ++m) {
+        const int e = slot_exponent(p, acc[m][ct]);  // whole wave
+        const int u = (wave * kRowTiles + m) * 2 + (q >> 1);
+        *reinterpret_cast<uint2*>(base + c * kRowBytes + ((u ^ c) * 16 + (q & 1) * 8)) = f16s_encode(acc[m][ct], e);
+        if (q == 0) lds.exps[(ct * 16 + c) * kTileRows + wave * kRowTiles + m] = static_cast<int8_t>(e);
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int ct = c0; ct < kCt && ct < c0 + kRound; ++ct) {
+      Stage& buf = (ct - c0) / kPerBuf == 0 ? lds.s0 : (ct - c0) / kPerBuf == 1 ? lds.s1 : lds.s2;
+      const char* base = reinterpret_cast<const char*>(&buf) + (ct - c0) % kPerBuf * 16 * kRowBytes;
+#pragma unroll
+      for (int r0 = 0; r0 < 16; r0 += kRowsPass) {
+        const int r = r0 + static_cast<int>(threadIdx.x) / kUnits, u = threadIdx.x % kUnits;
+        const int col = ct * 16 + r;
+        if (r < 16 && col < g.n && u < units)
+          *reinterpret_cast<uint4*>(hv + static_cast<size_t>(lds.dst[col]) * H + bx * kTileRows * 16 + u * 8) =
+              *reinterpret_cast<const uint4*>(base + r * kRowBytes + (u ^ r) * 16);
       }
     }
   }
+  if (static_cast<int>(threadIdx.x) < g.n) {  // 8 or 16 exponents of the row
+    const size_t d = static_cast<size_t>(lds.dst[threadIdx.x]) * (H >> 4) + bx * kTileRows;
+    const uint2* es = reinterpret_cast<const uint2*>(lds.exps + threadIdx.x * kTileRows);
+#pragma unroll
+    for (int i = 0; i < kTileRows / 8; ++i)
+      if (i * 16 < units) reinterpret_cast<uint2*>(ev + d)[i] = es[i];
+  }
 }
 
+// The code of the smallest even number of token tiles that holds the item.
+template <bool kGateUp, int kRowTiles, int kWaves, int kSteps, bool kStream>
+__device__ __forceinline__ void tile_tokens(const FfnParams& p, const Group& g, int bx,
+                                            const TileLds<kWaves, kSteps>& lds) {
+  if (g.n > 96)
+    tile_body<kGateUp, kRowTiles, kWaves, kSteps, kStream, 8>(p, g, bx, lds);
+  else if (g.n > 64)
+    tile_body<kGateUp, kRowTiles, kWaves, kSteps, kStream, 6>(p, g, bx, lds);
+  else if (g.n > 32)
+    tile_body<kGateUp, kRowTiles, kWaves, kSteps, kStream, 4>(p, g, bx, lds);
+  else
+    tile_body<kGateUp, kRowTiles, kWaves, kSteps, kStream, 2>(p, g, bx, lds);
+}
 
-template <bool kGateUp, int kRowTiles>
-__global__ __launch_bounds__(kThreads, 2) void ffn_tile_bf16_kernel(FfnParams p, int gx) {
+template <bool kGateUp, int kRowTiles, int kWaves, int kSteps, int kMinWaves>
+__global__ __launch_bounds__(kWaves * kWave, kMinWaves) void ffn_tile_bf16_kernel(FfnParams p, int gx) {
   int item, bx;
   if (!map_item(p, gx, item, bx)) return;
   Group g;
   if (!decode_item(item, p.shared_items, p.max_work, p.n_work, p.work, p.row_token, p.T, p.Tk, p.E, g)) return;
-  __shared__ bf16x8 stage[2][kStageSteps][kTileTok][kWave];  // 32 KiB
+  __shared__ TokStage<kSteps> s0, s1, s2;
+  __shared__ int dst[kGateUp ? 1 : DMOE_WORK_ROWS];
+  __shared__ __align__(16) int8_t exps[kGateUp ? 16 : DMOE_WORK_ROWS * kWaves * kRowTiles];
+  const TileLds<kWaves, kSteps> lds{s0, s1, s2, dst, exps};
   // An expert whose rows are one item is the only reader of its weights in
   // the launch (each row block reads its own rows once): they are streamed
   // non-temporally, which measured faster.  The items of an expert with more
@@ -483,9 +609,9 @@ __global__ __launch_bounds__(kThreads, 2) void ffn_tile_bf16_kernel(FfnParams p,
     single = p.T <= DMOE_WORK_ROWS;
   }
   if (single)
-    tile_body<kGateUp, kRowTiles, true>(p, g, bx, stage);
+    tile_tokens<kGateUp, kRowTiles, kWaves, kSteps, true>(p, g, bx, lds);
   else
-    tile_body<kGateUp, kRowTiles, false>(p, g, bx, stage);
+    tile_tokens<kGateUp, kRowTiles, kWaves, kSteps, false>(p, g, bx, lds);
 }
 
 // ---- launch ---------------------------------------------------------------
@@ -551,26 +677,50 @@ hipError_t launch_bf16(const FfnParams& p, int ldh, int groups, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Tile kernels, one item per workgroup: two weight tiles per wave
-// halve the LDS reads per weight byte; one tile per wave doubles the
-// workgroups.  A gate/up grid of fewer than two rounds of the chip (three
-// resident workgroups on each of 256 CUs) ends in a long partial round, which
-// the finer split shortens.  The down projection always takes two tiles per
-// wave: its reduction (I) is short, and at one tile per wave a workgroup
-// reads twice as many token bytes as weight bytes.
+// Tile kernels, one item per workgroup.  Two weight tiles per wave halve the
+// LDS reads per weight byte; one tile per wave doubles the workgroups.  A
+// gate/up grid of fewer than two rounds of the chip (three resident
+// workgroups on each of 256 CUs) ends in a long partial round, which the
+// finer split shortens.  The down projection always takes two tiles per wave:
+// its reduction (I) is short, and at one tile per wave a workgroup reads
+// twice as many token bytes as weight bytes.
+//
+// Wide workgroups (eight waves, 256 weight rows, one K-step per stage so that
+// two of them fit a CU) read a quarter fewer bytes per flop than the four-wave
+// ones, but leave fewer, longer workgroups to balance.  Whole layer, us,
+// four waves -> wide, on layers of the decode shape (hidden 2048, 256 experts
+// of intermediate 512, top-8): gate/up wide at 64 x 64 tokens 441 -> 431,
+// 32 x 64 319 -> 302, 64 x 32 360 -> 345 (wide grids of 1088 workgroups and
+// up, 43 rows per item and up); the Zipf-biased hidden-4096 layer of 8 x 32
+// tokens 173 -> 196 (792 workgroups, 32 rows), 512 tokens under Top-P
+// 298 -> 304 (15 rows).  Down wide as well: 64 x 64 431 -> 428 (4352
+// workgroups), 32 x 64 302 -> 312 (2176), 64 x 32 345 -> 352 (3200).
 constexpr long kTileRound = 3L * 256;
+constexpr int kWideMinRows = 32;                             // rows per item
+constexpr long kWideMinGateUp = 1024, kWideMinDown = 4096;  // workgroups of the wide grid
+
 template <bool kGateUp>
-hipError_t launch_tile_bf16(const FfnParams& p, int ldh, int items, hipStream_t s) {
+hipError_t launch_tile_bf16(const FfnParams& p, int ldh, int items, long rows, hipStream_t s) {
   const int tiles = kGateUp ? ldh / 8 : p.H / 16;  // packed 16-row tiles
   const int items8 = (items + 7) / 8 * 8;
   if constexpr (kGateUp) {
     if (static_cast<long>(ldh / 64) * items < 2 * kTileRound) {
-      ffn_tile_bf16_kernel<true, 1><<<dim3(tiles / 4 * items8), kThreads, 0, s>>>(p, tiles / 4);
+      ffn_tile_bf16_kernel<true, 1, 4, 2, 2><<<dim3(tiles / 4 * items8), 4 * kWave, 0, s>>>(p, tiles / 4);
       return hipGetLastError();
     }
   }
-  ffn_tile_bf16_kernel<kGateUp, 2><<<dim3(tiles / 8 * items8), kThreads, 0, s>>>(p, tiles / 8);
+  const int wide = (tiles + 15) / 16;
+  if (rows >= kWideMinRows && static_cast<long>(wide) * items >= (kGateUp ? kWideMinGateUp : kWideMinDown))
+    ffn_tile_bf16_kernel<kGateUp, 2, 8, 1, 4><<<dim3(wide * items8), 8 * kWave, 0, s>>>(p, wide);
+  else
+    ffn_tile_bf16_kernel<kGateUp, 2, 4, 2, 2><<<dim3(tiles / 8 * items8), 4 * kWave, 0, s>>>(p, tiles / 8);
   return hipGetLastError();
+}
+
+hipError_t launch_tiles(const FfnParams& p, int ldh, int items, long rows, hipStream_t s) {
+  const hipError_t err = launch_tile_bf16<true>(p, ldh, items, rows, s);
+  if (err != hipSuccess) return err;
+  return launch_tile_bf16<false>(p, ldh, items, rows, s);
 }
 
 constexpr int kPassRows = 16;  // token rows of one decode-kernel pass
@@ -602,9 +752,7 @@ hipError_t launch_ffn(const FfnArgs& a, dmoe_dtype dt, hipStream_t s) {
                 static_cast<bf16_t*>(a.workspace), a.slot_out, a.shared_out,
                 a.slot_fmt == DMOE_SLOT_F16S ? 1 : 0};
     if (use_tile_kernels(a.T, a.k, a.max_work, items, ldh)) {
-      const hipError_t err = launch_tile_bf16<true>(p, ldh, items, s);
-      if (err != hipSuccess) return err;
-      return launch_tile_bf16<false>(p, ldh, items, s);
+      return launch_tiles(p, ldh, items, rows_per_item(a.T, a.k, a.max_work), s);
     }
     switch (pick_ntiles(a.T, a.k, a.max_work)) {
       case 1: {
@@ -624,9 +772,7 @@ hipError_t launch_ffn(const FfnArgs& a, dmoe_dtype dt, hipStream_t s) {
         const bool multi_burst = a.H / 128 > Shape<1>::kGuMax || ldh / 128 > Shape<1>::kDnMax;
         const bool pass_per_expert = static_cast<long>(a.T) * a.k >= static_cast<long>(kPassRows) * a.E;
         if (a.T > kPassRows && (multi_burst || pass_per_expert)) {
-          const hipError_t err = launch_tile_bf16<true>(p, ldh, items, s);
-          if (err != hipSuccess) return err;
-          return launch_tile_bf16<false>(p, ldh, items, s);
+          return launch_tiles(p, ldh, items, rows_per_item(a.T, a.k, a.max_work), s);
         }
         return launch_bf16<1>(p, ldh, items, s);
       }
