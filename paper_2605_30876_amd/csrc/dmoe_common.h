@@ -145,8 +145,8 @@ hipError_t launch_block_topp(const float* probs, int nb, int bs, int E, int k, f
 bool topp_supported(int bs, int E, int k);
 
 // The whole routing stage: router, selection (blocks of gs tokens when block,
-// else per token), combine weights and schedule.  Small forwards run the
-// selection and schedule in one workgroup after the router; others chain the
+// else per token), combine weights and schedule.  Blocks that fit in LDS run
+// everything after the router in one workgroup each; others chain the
 // separate launchers.  Results are identical either way.
 struct RouteArgs {
   const void* x;
@@ -172,7 +172,6 @@ struct RouteArgs {
   int32_t* coreset_size = nullptr;
 };
 hipError_t launch_route(const RouteArgs& a, dmoe_dtype dt, hipStream_t s);
-bool route_fused_fits(int T, int E, int k, int gs, bool block);
 
 // 16-byte chunks: elements of one chunk of the chunk-major activation layout.
 inline int chunk_elems(dmoe_dtype dt) { return dt == DMOE_F32 ? 4 : 8; }

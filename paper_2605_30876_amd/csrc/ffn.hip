@@ -119,7 +119,7 @@ using namespace fdev;  // the wave-level operand helpers of ffn_dev.h
 // Occupancy floors (waves per SIMD) for the two-tile variants, which serve
 // block-routed decode steps: 3 (gate/up and down) keep every workgroup of
 // such a launch resident at once instead of leaving a second partial round.
-// grid (ldh / (8 RT), groups): packed gate/up tiles it .. it + RT - 1, tile
+// grid (ldh / (8 RT), groups, passes): packed gate/up tiles it .. it + RT - 1, tile
 // `it` = 8 intermediate units.
 // Wave w reduces over hidden chunks [w*H/32, (w+1)*H/32) (K-steps
 // [w*H/128, (w+1)*H/128)).
@@ -142,6 +142,12 @@ __global__ __launch_bounds__(kThreads, MINW) void ffn_gateup_bf16_kernel(FfnPara
   const int bstep = 32 * p.T;  // 4 chunks of T tokens per K-step
   const int chunk0 = wave * steps * 4 + q;
 
+  // One token tile: all passes here, over weights held in registers.  More:
+  // one pass per workgroup (grid z; these launches are small, and the passes
+  // of an item of many rows, the shared expert's above all, were their long
+  // pole: five blocks of 24 tokens over 48 experts 50.6 -> 47.8 us per layer).
+  constexpr bool kPassZ = NT > 1;
+  const int pz = kPassZ ? blockIdx.z * 16 * NT : 0, pend = kPassZ ? min(g.n, pz + 16 * NT) : g.n;
   __shared__ f32x4 red[3][RT][NT][kWave];
   WaveOps<NT, KMAX, BC, RT> w;  // a one-burst weight slice stays here across passes
   // At two token tiles (items of whole blocks) a one-burst slice is loaded
@@ -149,6 +155,7 @@ __global__ __launch_bounds__(kThreads, MINW) void ffn_gateup_bf16_kernel(FfnPara
   // item, not for its row list and then x.  With one token tile (many small
   // items) the token fragments going first measured faster.
   bool a_held = false;
+  if (kPassZ && pz >= g.n) return;
   if constexpr (NT == 2) {
     if (steps <= KMAX) {
       issue_a<true>(w, pa, tstride, steps);
@@ -156,7 +163,7 @@ __global__ __launch_bounds__(kThreads, MINW) void ffn_gateup_bf16_kernel(FfnPara
       __builtin_amdgcn_sched_barrier(0);
     }
   }
-  for (int p0 = 0; p0 < g.n; p0 += 16 * NT) {
+  for (int p0 = pz; p0 < pend; p0 += 16 * NT) {
     const bf16_t* pb[NT];
     int tok[NT];
     bool gathered = false;
@@ -172,7 +179,7 @@ __global__ __launch_bounds__(kThreads, MINW) void ffn_gateup_bf16_kernel(FfnPara
                         : p.xk + (static_cast<size_t>(chunk0) * p.T + tok[ct]) * 8;
     f32x4 acc[RT][NT];
     zero(acc);
-    wave_dot<true>(w, pa, tstride, pb, gathered ? 32 : bstep, steps, acc, a_held || (p0 > 0 && steps <= KMAX));
+    wave_dot<true>(w, pa, tstride, pb, gathered ? 32 : bstep, steps, acc, a_held || (p0 > pz && steps <= KMAX));
     reduce_waves(acc, red, wave, lane);
     if (wave == 0) {
 #pragma unroll
@@ -194,7 +201,7 @@ __global__ __launch_bounds__(kThreads, MINW) void ffn_gateup_bf16_kernel(FfnPara
   }
 }
 
-// grid (H / (16 RT), groups): packed down tiles jt .. jt + RT - 1, tile `jt`
+// grid (H / (16 RT), groups, passes): packed down tiles jt .. jt + RT - 1, tile `jt`
 // = 16 output features.
 template <int NT, int KMAX, int BC, int MINW, bool kSharedFirst, int RT>
 __global__ __launch_bounds__(kThreads, MINW) void ffn_down_bf16_kernel(FfnParams p) {
@@ -216,7 +223,9 @@ __global__ __launch_bounds__(kThreads, MINW) void ffn_down_bf16_kernel(FfnParams
 
   __shared__ f32x4 red[3][RT][NT][kWave];
   WaveOps<NT, KMAX, BC, RT> w;  // a one-burst weight slice stays here across passes
-  for (int p0 = 0; p0 < g.n; p0 += 16 * NT) {
+  constexpr bool kPassZ = NT > 1;
+  const int pz = kPassZ ? blockIdx.z * 16 * NT : 0, pend = kPassZ ? min(g.n, pz + 16 * NT) : g.n;
+  for (int p0 = pz; p0 < pend; p0 += 16 * NT) {
     const bf16_t* pb[NT];
 #pragma unroll
     for (int ct = 0; ct < NT; ++ct) {
@@ -225,7 +234,7 @@ __global__ __launch_bounds__(kThreads, MINW) void ffn_down_bf16_kernel(FfnParams
     }
     f32x4 acc[RT][NT];
     zero(acc);
-    wave_dot<true>(w, pa, tstride, pb, bstep, steps, acc, p0 > 0 && steps <= KMAX);
+    wave_dot<true>(w, pa, tstride, pb, bstep, steps, acc, p0 > pz && steps <= KMAX);
     reduce_waves(acc, red, wave, lane);
     if (wave == 0) {
 #pragma unroll
@@ -668,12 +677,13 @@ struct Shape<4> {
 template <int NT>
 hipError_t launch_bf16(const FfnParams& p, int ldh, int groups, hipStream_t s) {
   using S = Shape<NT>;
+  const int passes = NT > 1 ? (std::min(p.T, DMOE_WORK_ROWS) + 16 * NT - 1) / (16 * NT) : 1;
   ffn_gateup_bf16_kernel<NT, S::kGuMax, S::kGuChunk, S::kGuWaves, S::kSharedFirst, S::kGuRows>
-      <<<dim3(ldh / (8 * S::kGuRows), groups), kThreads, 0, s>>>(p);
+      <<<dim3(ldh / (8 * S::kGuRows), groups, passes), kThreads, 0, s>>>(p);
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
   ffn_down_bf16_kernel<NT, S::kDnMax, S::kDnChunk, S::kDnWaves, S::kSharedFirst, S::kDnRows>
-      <<<dim3(p.H / (16 * S::kDnRows), groups), kThreads, 0, s>>>(p);
+      <<<dim3(p.H / (16 * S::kDnRows), groups, passes), kThreads, 0, s>>>(p);
   return hipGetLastError();
 }
 

@@ -167,72 +167,6 @@ __global__ __launch_bounds__(kRouterWaves * kWave) void layer_router_kernel(Laye
 
 constexpr int kRoundsMax = dev::kMaxK + 1;
 
-// The first `rounds` of S[0..E) (LDS; E <= kThreads, rounds <= 16) in (score
-// desc, id asc) order, by all threads of the workgroup; the same selection
-// as dev::wave_topk_radix.  Thread e holds expert e's order key.  A lower
-// bound of the rounds-th largest key: the rounds-th largest of the maxima of
-// the 16-lane groups (each of those groups holds an element at least that
-// large).  Only keys at or above it are candidates, and each candidate's rank
-// among them, by (key, id), is its rank in the row.  Called by all threads.
-constexpr int kCandMax = kThreads;
-__device__ void block_topk_small(const float* S, int E, int rounds, int* sel, float* selv, uint32_t* gmax,
-                                 uint32_t* ckey, int* cid, int* wcount) {
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  // excluded threads (e >= E) take key 0, below every real key (real keys >= 1)
-  const uint32_t key = tid < E ? max(dev::order_key(S[tid]), 1u) : 0u;
-  uint32_t g = key;  // max over the 16 lanes of the row: rotations by 1, 2, 4, 8
-  g = max(g, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(g), 0x121, 0xF, 0xF, false)));
-  g = max(g, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(g), 0x122, 0xF, 0xF, false)));
-  g = max(g, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(g), 0x124, 0xF, 0xF, false)));
-  g = max(g, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(g), 0x128, 0xF, 0xF, false)));
-  if ((lane & 15) == 0) gmax[tid >> 4] = g;
-  __syncthreads();
-  if (tid < 16) {  // rank of group tid's maximum among the 16 (ties by group index)
-    const uint32_t mine = gmax[tid];
-    int r = 0;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) r += dev::key_before(gmax[i], i, mine, tid) ? 1 : 0;
-    if (r == rounds - 1) gmax[16] = mine;
-  }
-  __syncthreads();
-  const uint32_t bound = gmax[16];
-  const bool cand = key >= bound && tid < E;
-  const uint64_t m = __ballot(cand);
-  if (lane == 0) wcount[wave] = __popcll(m);
-  __syncthreads();
-  int base = 0, ncand = 0;
-#pragma unroll
-  for (int w = 0; w < kThreads / kWave; ++w) {
-    base += w < wave ? wcount[w] : 0;
-    ncand += wcount[w];
-  }
-  if (cand) {
-    const int pos = base + dev::lanes_below(m);
-    ckey[pos] = key;
-    cid[pos] = tid;
-  }
-  if (tid < 3) {  // pad to a multiple of 4 with entries that rank after everything
-    ckey[ncand + tid] = 0u;
-    cid[ncand + tid] = dev::kNone;
-  }
-  __syncthreads();
-  if (cand) {
-    int r = 0;
-    const uint4* k4 = reinterpret_cast<const uint4*>(ckey);
-    const int4* i4 = reinterpret_cast<const int4*>(cid);
-    for (int i = 0; i < (ncand + 3) / 4; ++i) {
-      const uint4 kk = k4[i];
-      const int4 ii = i4[i];
-      r += (dev::key_before(kk.x, ii.x, key, tid) ? 1 : 0) + (dev::key_before(kk.y, ii.y, key, tid) ? 1 : 0) +
-           (dev::key_before(kk.z, ii.z, key, tid) ? 1 : 0) + (dev::key_before(kk.w, ii.w, key, tid) ? 1 : 0);
-    }
-    if (r < rounds) {
-      sel[r] = tid;
-      selv[r] = dev::key_value(key);
-    }
-  }
-}
-
 // LDS of the routing prologue (4-byte words): P [T][Es] probabilities, then
 // S [Es] block means.  Es = E rounded up to a multiple of 4.
 __host__ __device__ inline size_t prologue_words(int T, int E) {
@@ -393,10 +327,7 @@ __global__ __launch_bounds__(kThreads, 2) void layer_route_gateup_kernel(LayerPa
   __shared__ int slds[kWave];
   __shared__ float wslot[NT * kTok];
   __shared__ f32x4 red[kWaves - 1][kRTof<NT>][NT][kWave];
-  __shared__ uint32_t gmax[17];
-  __shared__ __align__(16) uint32_t ckey[kCandMax + 4];
-  __shared__ __align__(16) int cid[kCandMax + 4];
-  __shared__ int wcount[kWaves];
+  __shared__ dev::BlockTopkLds tk;
   constexpr int kRT = kRTof<NT>;
   const int T = p.T, E = p.E, k = p.k;
   const int Es = dev::pad4(E);
@@ -429,8 +360,8 @@ __global__ __launch_bounds__(kThreads, 2) void layer_route_gateup_kernel(LayerPa
   }
   __syncthreads();
   const int rounds = k < E ? k + 1 : k;
-  if (E <= kThreads && rounds <= 16) {
-    block_topk_small(S, E, rounds, sel, selv, gmax, ckey, cid, wcount);
+  if (dev::block_topk_fits(E, rounds)) {
+    dev::block_topk_small(S, E, rounds, sel, selv, tk);
   } else if (wave == 0) {
     dev::wave_topk_radix_n<4 * NQ>(S, E, rounds, sel, selv, bufv, bufi);
   }

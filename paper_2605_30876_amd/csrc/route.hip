@@ -5,11 +5,11 @@
 //
 // A decode step routes few tokens; its routing kernels are bound by memory
 // round trips (each kernel boundary adds a write, a cache flush and a re-read
-// from another XCD), not by arithmetic.  When the forward's logits fit in
-// LDS (T*E <= 8192), everything after the router runs in ONE workgroup with a
+// from another XCD), not by arithmetic.  When a block's logits fit in
+// LDS, everything after the router runs in one workgroup per block with a
 // single round trip: all partial logits are loaded at once, then softmax
-// rows (into LDS), block sums, radix-select top-k per block, combine weights
-// and the schedule run on chip.  (Token routing has T rows to select; spread
+// rows (into LDS), block sums, top-k and combine weights run on chip, and for
+// a forward of one block the schedule too.  (Token routing has T rows to select; spread
 // over T/4 workgroups it is faster, so it runs the softmax and each token's
 // selection in one launch of T/4 workgroups, then the schedule.)  The
 // arithmetic is that of
@@ -24,65 +24,63 @@ namespace {
 
 constexpr int kThreads = dev::kSchedThreads;  // the schedule's workgroup size
 constexpr int kWaves = kThreads / kWave;
-constexpr int kFusedMaxTE = 8192;                   // logits of the forward kept in LDS
 constexpr size_t kMaxLdsBytes = 64 * 1024 - 1024;   // headroom for static LDS
 
-// LDS words of the fused kernel (4-byte words; rows padded to a multiple of 4
+// LDS words of the block kernel (4-byte words; rows padded to a multiple of 4
 // floats for 128-bit reads).
 struct FusedLayout {
   int Es;  // padded row stride
-  size_t sb, sel, selv, expc, bufv, bufi, sched, total;
+  size_t sb, sel, selv, bufv, bufi, sched, total;
 };
 
-__host__ __device__ inline FusedLayout fused_layout(int T, int E, int k, int G) {
+__host__ __device__ inline FusedLayout fused_layout(int T, int E, int k) {
   FusedLayout L;
   L.Es = (E + 3) & ~3;
-  L.sb = static_cast<size_t>(T) * L.Es;                        // P [T][Es]
-  L.sel = L.sb + static_cast<size_t>(G) * L.Es;                // S [G][Es]
-  L.selv = L.sel + static_cast<size_t>(G) * (k + 1);           // sel [G][k+1]
-  L.expc = L.selv + static_cast<size_t>(G) * (k + 1);          // selv [G][k+1]
-  L.bufv = L.expc + static_cast<size_t>(G) * k;                // expert lists [G][k]
-  L.bufi = L.bufv + static_cast<size_t>(kWaves) * (k + 1);     // per-wave top-k gather
-  L.sched = (L.bufi + static_cast<size_t>(kWaves) * (k + 1) + 3) & ~static_cast<size_t>(3);  // 16-byte aligned
-  L.total = L.sched + dev::schedule_lds_ints(E);               // schedule scratch
+  L.sb = static_cast<size_t>(T) * L.Es;  // P [T][Es]
+  L.sel = L.sb + L.Es;                   // S [Es]
+  L.selv = L.sel + (k + 1);              // sel [k+1]
+  L.bufv = L.selv + (k + 1);             // selv [k+1]
+  L.bufi = L.bufv + (k + 1);             // top-k gather
+  L.sched = L.bufi + (k + 1);
+  L.total = L.sched + kWave;             // closed-form schedule scratch
   return L;
 }
 
 constexpr int kWBatch = 8;  // selected probabilities of a token loaded together
 
-// kPerBlock: workgroup b routes block b alone (T = gs rows of the forward's
-// T_all; the partial planes keep T_all rows) and the schedule is left to a
-// launch of its own.
-template <int NQ, bool kPerBlock = false>
+// Routes one block of T tokens.  kPerBlock: workgroup b routes block b of a
+// forward of T_all tokens (the partial planes have T_all rows), and the
+// schedule is left to a launch of its own; otherwise the block is the forward
+// and the kernel writes the (closed-form) schedule too.  Several small blocks
+// in one workgroup, with the general schedule built there as well, measured
+// slower than a workgroup each and a schedule launch even for two: five blocks
+// of 24 tokens over 48 experts 54.9 -> 47.8 us per layer, three 43.9 -> 40.1,
+// two 36.6 -> 35.5.
+template <int NQ, bool kPerBlock>
 __global__ __launch_bounds__(kThreads) void route_small_kernel(
-    const float* part, int S, const float* __restrict__ bias, int T, int E, int k, int gs,
+    const float* part, int S, const float* __restrict__ bias, int T, int E, int k,
     float* probs, float* __restrict__ logits, float* __restrict__ block_scores,
     int32_t* __restrict__ experts, float* __restrict__ cw, float* __restrict__ gap,
     dmoe_schedule sched, int T_all) {
   extern __shared__ float lds[];
+  __shared__ dev::BlockTopkLds tk;
   if (kPerBlock) {
     const size_t b = blockIdx.x;
-    part += b * gs * E;
-    probs += b * gs * E;
-    if (logits) logits += b * gs * E;
+    part += b * T * E;
+    probs += b * T * E;
+    if (logits) logits += b * T * E;
     if (block_scores) block_scores += b * E;
     experts += b * k;
-    cw += b * gs * k;
+    cw += b * T * k;
     if (gap) gap += b;
   }
-  const int G = T / gs;
-  const int K1 = k + 1;
-  const FusedLayout L = fused_layout(T, E, k, G);
+  const FusedLayout L = fused_layout(T, E, k);
   const int Es = L.Es;
   float* P = lds;
   float* Sb = lds + L.sb;
   int* sel = reinterpret_cast<int*>(lds + L.sel);
   float* selv = lds + L.selv;
-  int* expc = reinterpret_cast<int*>(lds + L.expc);
   const int tid = threadIdx.x, wave = tid >> 6;
-  float* bufv = lds + L.bufv + wave * K1;
-  int* bufi = reinterpret_cast<int*>(lds + L.bufi) + wave * K1;
-  int* slds = reinterpret_cast<int*>(lds + L.sched);
 
   // 1. router softmax: wave w owns rows w, w + 8, ...; a batch of RB rows
   //    has all of its partial loads in flight together, then each row is
@@ -115,80 +113,58 @@ __global__ __launch_bounds__(kThreads) void route_small_kernel(
   }
   __syncthreads();
 
-  // 2. selection: block means in token order, then sel[b][0..rounds) in
-  //    (score desc, id asc) order, one wave per block by radix selection
-  const int rounds = k < E ? K1 : k;
-  const float n_tok = static_cast<float>(gs);
-  for (int i = tid; i < G * E; i += kThreads) {
-    const int b = i / E, e = i - b * E;
-    const float* pb = P + static_cast<size_t>(b) * gs * Es + e;
+  // 2. selection: the block mean in token order, then sel[0..rounds) in
+  //    (score desc, id asc) order
+  const int rounds = k < E ? k + 1 : k;
+  const float n_tok = static_cast<float>(T);
+  for (int e = tid; e < E; e += kThreads) {
+    const float* pe = P + e;
     float acc = 0.f;
 #pragma unroll 8
-    for (int t = 0; t < gs; ++t) acc += pb[static_cast<size_t>(t) * Es];  // token order
+    for (int t = 0; t < T; ++t) acc += pe[static_cast<size_t>(t) * Es];  // token order
     const float v = acc / n_tok;
-    Sb[static_cast<size_t>(b) * Es + e] = v;
-    if (block_scores) block_scores[i] = v;
+    Sb[e] = v;
+    if (block_scores) block_scores[e] = v;
   }
   __syncthreads();
-  for (int b = wave; b < G; b += kWaves)
-    dev::wave_topk_radix_n<4 * NQ>(Sb + static_cast<size_t>(b) * Es, E, rounds, sel + b * K1, selv + b * K1, bufv,
-                                   bufi);
+  if (dev::block_topk_fits(E, rounds))
+    dev::block_topk_small(Sb, E, rounds, sel, selv, tk);
+  else if (wave == 0)
+    dev::wave_topk_radix_n<4 * NQ>(Sb, E, rounds, sel, selv, lds + L.bufv, reinterpret_cast<int*>(lds + L.bufi));
   __syncthreads();
 
-  // 3. expert lists, gaps, and every token's weights renormalised over its
-  //    group's selection (summed in slot order)
-  for (int i = tid; i < G * k; i += kThreads) {
-    const int g = i / k, j = i - g * k;
-    const int e = sel[g * K1 + j];
-    experts[i] = e;
-    expc[i] = e;
-  }
-  if (gap)
-    for (int g = tid; g < G; g += kThreads) gap[g] = k < E ? selv[g * K1 + k - 1] - selv[g * K1 + k] : INFINITY;
+  // 3. expert list, gap, and every token's weights renormalised over the
+  //    selection (summed in slot order)
+  if (tid < k) experts[tid] = sel[tid];
+  if (gap && tid == 0) gap[0] = k < E ? selv[k - 1] - selv[k] : INFINITY;
   // one thread per (token, slot); each sums its token's k values in slot order
   for (int i = tid; i < T * k; i += kThreads) {
     const int t = i / k, j = i - t * k;
-    const int g = t / gs;
     const float* prow = P + static_cast<size_t>(t) * Es;
-    const int* sg = sel + g * K1;
     float denom = 0.f;
     for (int j0 = 0; j0 < k; j0 += kWBatch) {
       float v[kWBatch];
 #pragma unroll
       for (int u = 0; u < kWBatch; ++u)
-        if (j0 + u < k) v[u] = prow[sg[j0 + u]];
+        if (j0 + u < k) v[u] = prow[sel[j0 + u]];
 #pragma unroll
       for (int u = 0; u < kWBatch; ++u)
         if (j0 + u < k) denom += v[u];
     }
-    cw[i] = prow[sg[j]] / denom;
+    cw[i] = prow[sel[j]] / denom;
   }
-  __syncthreads();
-
-  // 4. unique-expert schedule of the G expert lists (one block: closed form)
   if (kPerBlock) return;
-  if (G == 1 && k <= kWave)
-    dev::schedule_one_group(expc, gs, k, slds, sched);
-  else
-    dev::schedule_wg(expc, G, gs, k, E, slds, sched);
+
+  // 4. the closed-form schedule of one block
+  dev::schedule_one_group(sel, T, k, reinterpret_cast<int*>(lds + L.sched), sched);
 }
 
 }  // namespace
 
-bool route_fused_fits(int T, int E, int k, int gs, bool block) {
-  // Token routing selects T rows serially per wave on one CU, slower than the
-  // separate kernels spread over T/4 workgroups: only block routing is fused.
-  if (!block) return false;
-  if (E > dev::kRegSoftmaxMaxE || k > dev::kMaxK) return false;
-  if (static_cast<long>(T) * E > kFusedMaxTE) return false;
-  return fused_layout(T, E, k, T / gs).total * sizeof(float) <= kMaxLdsBytes;
-}
-
 // One workgroup per block when a block's rows fit in LDS.
-static bool route_block_fits(int gs, int E, int k, bool block) {
-  if (!block) return false;
+static bool route_block_fits(int gs, int E, int k) {
   if (E > dev::kRegSoftmaxMaxE || k > dev::kMaxK) return false;
-  return fused_layout(gs, E, k, 1).total * sizeof(float) <= kMaxLdsBytes;
+  return fused_layout(gs, E, k).total * sizeof(float) <= kMaxLdsBytes;
 }
 
 // Alg. 1 with the Top-P coreset: the router, every token's own top-k (with
@@ -221,38 +197,28 @@ static hipError_t launch_route_topp(const RouteArgs& a, dmoe_dtype dt, hipStream
 hipError_t launch_route(const RouteArgs& a, dmoe_dtype dt, hipStream_t s) {
   if (a.topp) return launch_route_topp(a, dt, s);
   const int G = a.block ? a.T / a.gs : a.T;
-  if (route_fused_fits(a.T, a.E, a.k, a.gs, a.block)) {
+  if (a.block && route_block_fits(a.gs, a.E, a.k)) {
     float* part = nullptr;
     int S = 1;
     hipError_t err = launch_router_partials(a.x, a.w, dt, a.T, a.H, a.E, a.probs, a.x_chunked, a.workspace,
                                             a.ws_bytes, s, &part, &S);
     if (err != hipSuccess) return err;
-    const size_t lds = fused_layout(a.T, a.E, a.k, G).total * sizeof(float);
+    const size_t lds = fused_layout(a.gs, a.E, a.k).total * sizeof(float);
+#define DMOE_ROUTE_BLOCK(NQ_, PER_)                                                                               \
+  route_small_kernel<NQ_, PER_><<<G, kThreads, lds, s>>>(part, S, a.bias, a.gs, a.E, a.k, a.probs, a.logits,      \
+                                                         a.block_scores, a.experts, a.combine_w, a.gap, a.sched, a.T)
+    if (G == 1) {
+      if (a.E <= 256)
+        DMOE_ROUTE_BLOCK(1, false);
+      else
+        DMOE_ROUTE_BLOCK(2, false);
+      return hipGetLastError();
+    }
     if (a.E <= 256)
-      route_small_kernel<1><<<1, kThreads, lds, s>>>(part, S, a.bias, a.T, a.E, a.k, a.gs, a.probs, a.logits,
-                                                     a.block_scores, a.experts, a.combine_w, a.gap, a.sched, a.T);
+      DMOE_ROUTE_BLOCK(1, true);
     else
-      route_small_kernel<2><<<1, kThreads, lds, s>>>(part, S, a.bias, a.T, a.E, a.k, a.gs, a.probs, a.logits,
-                                                     a.block_scores, a.experts, a.combine_w, a.gap, a.sched, a.T);
-    return hipGetLastError();
-  }
-  if (route_block_fits(a.gs, a.E, a.k, a.block)) {
-    // larger block-routed forwards: one workgroup per block (softmax rows,
-    // block mean, top-k, weights), then the schedule
-    float* part = nullptr;
-    int S = 1;
-    hipError_t err = launch_router_partials(a.x, a.w, dt, a.T, a.H, a.E, a.probs, a.x_chunked, a.workspace,
-                                            a.ws_bytes, s, &part, &S);
-    if (err != hipSuccess) return err;
-    const size_t lds = fused_layout(a.gs, a.E, a.k, 1).total * sizeof(float);
-    if (a.E <= 256)
-      route_small_kernel<1, true><<<G, kThreads, lds, s>>>(part, S, a.bias, a.gs, a.E, a.k, a.gs, a.probs,
-                                                           a.logits, a.block_scores, a.experts, a.combine_w,
-                                                           a.gap, a.sched, a.T);
-    else
-      route_small_kernel<2, true><<<G, kThreads, lds, s>>>(part, S, a.bias, a.gs, a.E, a.k, a.gs, a.probs,
-                                                           a.logits, a.block_scores, a.experts, a.combine_w,
-                                                           a.gap, a.sched, a.T);
+      DMOE_ROUTE_BLOCK(2, true);
+#undef DMOE_ROUTE_BLOCK
     err = hipGetLastError();
     if (err != hipSuccess) return err;
     return launch_schedule(a.experts, G, a.gs, a.k, a.E, a.sched, s);

@@ -488,6 +488,84 @@ __device__ inline void wave_topk_radix(const float* row, int E, int rounds, int*
     wave_topk_radix_n<16>(row, E, rounds, sel, selv, buf_v, buf_i);
 }
 
+// ---- top-k by a whole workgroup --------------------------------------------
+// The first `rounds` of S[0..E) (LDS) in (score desc, id asc) order, by a
+// workgroup of at least kBlockTopkE threads; the same selection as
+// wave_topk_radix.  Thread e < kBlockTopkE holds expert e's order key.  A
+// lower bound of the rounds-th largest key: the rounds-th largest of the
+// maxima of the 16-lane groups (each of those groups holds an element at
+// least that large).  Only keys at or above it are candidates, and each
+// candidate's rank among them, by (key, id), is its rank in the row.  Called
+// by all threads; sel and selv are complete after the caller's next barrier.
+constexpr int kBlockTopkE = 256;
+constexpr int kBlockTopkRounds = kBlockTopkE / 16;
+struct BlockTopkLds {
+  uint32_t gmax[kBlockTopkE / 16 + 1];
+  __align__(16) uint32_t ckey[kBlockTopkE + 4];
+  __align__(16) int cid[kBlockTopkE + 4];
+  int wcount[kBlockTopkE / kWave];
+};
+__host__ __device__ constexpr bool block_topk_fits(int E, int rounds) {
+  return E <= kBlockTopkE && rounds <= kBlockTopkRounds;
+}
+__device__ inline void block_topk_small(const float* S, int E, int rounds, int* sel, float* selv, BlockTopkLds& l) {
+  constexpr int kGroups = kBlockTopkE / 16, kW = kBlockTopkE / kWave;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  // excluded threads (e >= E) take key 0, below every real key (real keys >= 1)
+  const uint32_t key = tid < E ? max(order_key(S[tid]), 1u) : 0u;
+  uint32_t g = key;  // max over the 16 lanes of the row: rotations by 1, 2, 4, 8
+  g = max(g, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(g), 0x121, 0xF, 0xF, false)));
+  g = max(g, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(g), 0x122, 0xF, 0xF, false)));
+  g = max(g, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(g), 0x124, 0xF, 0xF, false)));
+  g = max(g, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(g), 0x128, 0xF, 0xF, false)));
+  if ((lane & 15) == 0 && tid < kBlockTopkE) l.gmax[tid >> 4] = g;
+  __syncthreads();
+  if (tid < kGroups) {  // rank of group tid's maximum among the groups (ties by group index)
+    const uint32_t mine = l.gmax[tid];
+    int r = 0;
+#pragma unroll
+    for (int i = 0; i < kGroups; ++i) r += key_before(l.gmax[i], i, mine, tid) ? 1 : 0;
+    if (r == rounds - 1) l.gmax[kGroups] = mine;
+  }
+  __syncthreads();
+  const uint32_t bound = l.gmax[kGroups];
+  const bool cand = key >= bound && tid < E;
+  const uint64_t m = __ballot(cand);
+  if (lane == 0 && wave < kW) l.wcount[wave] = __popcll(m);
+  __syncthreads();
+  int base = 0, ncand = 0;
+#pragma unroll
+  for (int w = 0; w < kW; ++w) {
+    base += w < wave ? l.wcount[w] : 0;
+    ncand += l.wcount[w];
+  }
+  if (cand) {
+    const int pos = base + lanes_below(m);
+    l.ckey[pos] = key;
+    l.cid[pos] = tid;
+  }
+  if (tid < 3) {  // pad to a multiple of 4 with entries that rank after everything
+    l.ckey[ncand + tid] = 0u;
+    l.cid[ncand + tid] = kNone;
+  }
+  __syncthreads();
+  if (cand) {
+    int r = 0;
+    const uint4* k4 = reinterpret_cast<const uint4*>(l.ckey);
+    const int4* i4 = reinterpret_cast<const int4*>(l.cid);
+    for (int i = 0; i < (ncand + 3) / 4; ++i) {
+      const uint4 kk = k4[i];
+      const int4 ii = i4[i];
+      r += (key_before(kk.x, ii.x, key, tid) ? 1 : 0) + (key_before(kk.y, ii.y, key, tid) ? 1 : 0) +
+           (key_before(kk.z, ii.z, key, tid) ? 1 : 0) + (key_before(kk.w, ii.w, key, tid) ? 1 : 0);
+    }
+    if (r < rounds) {
+      sel[r] = tid;
+      selv[r] = key_value(key);
+    }
+  }
+}
+
 // ---- unique-expert schedule (one workgroup of kSchedThreads) ---------------
 
 constexpr int kSchedThreads = 512;
@@ -564,6 +642,76 @@ __device__ inline void schedule_totals(int c, int gs, int E, const dmoe_schedule
   }
 }
 
+// schedule_wg for at most kSchedThreads entries (decode steps): one round, so
+// the entries are read once and the round's bitmasks also give the counts.
+__device__ inline void schedule_one_round(const int32_t* experts, int n_entries, int gs, int k, int E, int* lds,
+                                          const dmoe_schedule& sched, bool place_rows) {
+  const int Ep = pad4(E);
+  int* base = lds;                                          // [E'] first row
+  unsigned* mask = reinterpret_cast<unsigned*>(base + Ep);  // [E'][kMaskWords]
+  int* pos = reinterpret_cast<int*>(mask + static_cast<size_t>(Ep) * kMaskWords);  // [kSchedThreads]
+  const int tid = threadIdx.x;
+  const int e = tid < n_entries ? experts[tid] : -1;
+  const bool active = e >= 0 && e < E;
+  for (int i = tid; i < Ep * (kMaskWords / 4); i += kSchedThreads)
+    reinterpret_cast<uint4*>(mask)[i] = make_uint4(0u, 0u, 0u, 0u);
+  __syncthreads();
+  const int word = tid >> 5;
+  const unsigned bit = 1u << (tid & 31);
+  if (active) atomicOr(&mask[e * kMaskWords + word], bit);
+  __syncthreads();
+  int cnt = 0;
+  if (tid < E) {
+    const uint4* m4 = reinterpret_cast<const uint4*>(mask + tid * kMaskWords);
+#pragma unroll
+    for (int w = 0; w < kMaskWords / 4; ++w) {
+      const uint4 m = m4[w];
+      cnt += __popc(m.x) + __popc(m.y) + __popc(m.z) + __popc(m.w);
+    }
+  }
+  schedule_totals(cnt, gs, E, sched, base);
+  if (!place_rows) return;
+  int below = 0;
+  if (active) {
+    const uint4* m4 = reinterpret_cast<const uint4*>(mask + e * kMaskWords);
+#pragma unroll
+    for (int w4 = 0; w4 < kMaskWords / 4; ++w4) {
+      const uint4 q = m4[w4];
+      const unsigned m[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int w = 4 * w4 + u;
+        below += w < word ? __popc(m[u]) : (w == word ? __popc(m[u] & (bit - 1u)) : 0);
+      }
+    }
+  }
+  __syncthreads();  // base
+  const int g = tid / k, slot = tid - g * k;
+  const int first = active ? base[e] + below * gs : -1;  // an id outside [0, E): no rows
+  if (gs == 1) {
+    if (active) {
+      sched.row_token[first] = g;
+      sched.row_slot[first] = slot;
+    }
+    return;
+  }
+  pos[tid] = first;
+  __syncthreads();
+  // an entry's gs rows by 2^sh lanes, several entries per wave
+  int sh = 0;
+  while ((1 << sh) < gs && sh < 6) ++sh;
+  const int per = kSchedThreads >> sh, l0 = tid & ((1 << sh) - 1);
+  for (int ie = tid >> sh; ie < n_entries; ie += per) {
+    const int p = pos[ie];
+    if (p < 0) continue;
+    const int ig = ie / k, j = ie - ig * k;
+    for (int tl = l0; tl < gs; tl += 1 << sh) {
+      sched.row_token[p + tl] = ig * gs + tl;
+      sched.row_slot[p + tl] = j;
+    }
+  }
+}
+
 // Builds the schedule of n_groups expert lists of k (experts: global or LDS,
 // [n_groups][k]; group g covers tokens g*gs .. g*gs+gs-1).  Called by all
 // kSchedThreads threads of the workgroup; lds holds schedule_lds_ints(E) ints
@@ -579,6 +727,10 @@ __device__ inline void schedule_totals(int c, int gs, int E, const dmoe_schedule
 //      to a many-workgroup launch (schedule_rows_kernel).
 __device__ inline void schedule_wg(const int32_t* experts, int n_groups, int gs, int k, int E, int* lds,
                                    const dmoe_schedule& sched, bool place_rows = true) {
+  if (n_groups * k <= kSchedThreads) {
+    schedule_one_round(experts, n_groups * k, gs, k, E, lds, sched, place_rows);
+    return;
+  }
   int32_t* const row_token = sched.row_token;
   int32_t* const row_slot = sched.row_slot;
   const int Ep = pad4(E);
