@@ -653,17 +653,27 @@ int pick_ntiles(int T, int k, int max_work) {
 // kernel applies each h fragment to two weight tiles (half the h reads from
 // L2; measured 0.4 us faster per step than one tile, while two gate/up tiles
 // per wave measured 1.2 us slower).
+// Burst lengths set the registers and so the resident workgroups, which set
+// how much is in flight for workgroups of tens of KB: the one-tile down
+// kernel at bursts of four K-steps (intermediate 512 in one) holds five per
+// CU where eight-step bursts held three (32 tokens of the decode layer, token
+// routing 186 -> 179 us per layer, Top-P 106 -> 102; two bursts at
+// intermediate 1024 235 -> 234; forced to six per CU 201); the two-tile
+// gate/up kernel at eight steps holds four (five blocks of 24 tokens over 48
+// experts 47.2 -> 45.1, two blocks of 32 of the decode layer 56.5 -> 55.5).
+// Other gate/up bursts at one token tile measured within 1.5 % (four and
+// eight steps, one weight tile).
 template <int NT>
 struct Shape;
 template <>
 struct Shape<1> {
-  static constexpr int kGuMax = 16, kGuChunk = 4, kGuWaves = 2, kDnMax = 8, kDnChunk = 4, kDnWaves = 3;
+  static constexpr int kGuMax = 16, kGuChunk = 4, kGuWaves = 2, kDnMax = 4, kDnChunk = 4, kDnWaves = 4;
   static constexpr int kGuRows = 2, kDnRows = 2;
   static constexpr bool kSharedFirst = true;
 };
 template <>
 struct Shape<2> {
-  static constexpr int kGuMax = 16, kGuChunk = 4, kGuWaves = 3, kDnMax = 4, kDnChunk = 4, kDnWaves = 3;
+  static constexpr int kGuMax = 8, kGuChunk = 4, kGuWaves = 4, kDnMax = 4, kDnChunk = 4, kDnWaves = 3;
   static constexpr int kGuRows = 1, kDnRows = 2;
   static constexpr bool kSharedFirst = false;
 };
@@ -733,7 +743,8 @@ hipError_t launch_tiles(const FfnParams& p, int ldh, int items, long rows, hipSt
   return launch_tile_bf16<false>(p, ldh, items, rows, s);
 }
 
-constexpr int kPassRows = 16;  // token rows of one decode-kernel pass
+constexpr int kPassRows = 16;    // token rows of one decode-kernel pass
+constexpr int kSliceSteps = 16;  // K-steps of a wave's gate/up slice beyond which a schedule takes the tile kernels
 
 bool use_tile_kernels(int T, int k, int max_work, int items, int ldh) {
   return rows_per_item(T, k, max_work) >= 32 && static_cast<long>(ldh / 32) * items >= 512;
@@ -770,8 +781,8 @@ hipError_t launch_ffn(const FfnArgs& a, dmoe_dtype dt, hipStream_t s) {
         // still collect many (a popular expert, a small Top-P coreset, the
         // shared expert over more than 16 tokens).  The decode kernels keep a
         // wave's weight slice in registers across 16-row passes when it is
-        // one burst; when it is not, they would stream the weights once per
-        // pass, so such layers run every item on the tile kernels (measured
+        // one burst; long slices they would stream once per pass, so such
+        // layers run every item on the tile kernels (measured
         // faster than leaving the items of one pass to the decode kernels,
         // whose grids, sized for the worst case, cost ~17 us each when few
         // items are that small).  So do schedules of at least one pass per
@@ -779,7 +790,7 @@ hipError_t launch_ffn(const FfnArgs& a, dmoe_dtype dt, hipStream_t s) {
         // faster too (512 tokens over 256 experts at hidden 2048: token
         // routing 321 -> 283 us, Top-P 317 -> 306; 256 tokens and fewer
         // favour the decode kernels).
-        const bool multi_burst = a.H / 128 > Shape<1>::kGuMax || ldh / 128 > Shape<1>::kDnMax;
+        const bool multi_burst = a.H / 128 > kSliceSteps || ldh / 128 > kSliceSteps / 2;
         const bool pass_per_expert = static_cast<long>(a.T) * a.k >= static_cast<long>(kPassRows) * a.E;
         if (a.T > kPassRows && (multi_burst || pass_per_expert)) {
           return launch_tiles(p, ldh, items, rows_per_item(a.T, a.k, a.max_work), s);
