@@ -129,6 +129,96 @@ __device__ __forceinline__ void wave_dot(WaveOps<NT, KMAX, BC, RT>& w, const bf1
   }
 }
 
+// wave_dot for one full burst (KMAX steps, straight-line: the compiler's wait
+// counts are exact) with three token chunk buffers: chunks
+// and their weights are issued alternately, so that a chunk's tokens return
+// with its weights.  (With two buffers, chunk C + 1 is issued once chunk C - 1
+// is done: after the weights have arrived, the last chunks each wait for a
+// round trip of their own.)
+template <int NT, int KMAX, int BC, int RT>
+struct WaveOps3 {
+  static constexpr int kChunks = KMAX / BC;
+  static_assert(kChunks == 4, "four chunks");
+  bf16x8 a[RT][KMAX];
+  bf16x8 b[3][BC][NT];
+};
+
+// Token chunk C of a full burst into its buffer: step s of tile ct at pb +
+// s*bstep + lb[ct] (pb uniform over the wave: the loads take a scalar base and
+// a 32-bit lane offset, which leaves the registers to the operands).
+template <int C, int NT, int KMAX, int BC, int RT>
+__device__ __forceinline__ void issue_b3(WaveOps3<NT, KMAX, BC, RT>& w, const bf16_t* pb, const uint32_t (&lb)[NT],
+                                         int bstep) {
+#pragma unroll
+  for (int s = 0; s < BC; ++s)
+#pragma unroll
+    for (int ct = 0; ct < NT; ++ct) w.b[C % 3][s][ct] = ld_bf16x8(pb + (C * BC + s) * bstep + lb[ct]);
+}
+
+// pa is uniform too, la the lane's offset.
+template <bool kStream, int NT, int KMAX, int BC, int RT>
+__device__ __forceinline__ void wave_dot_burst(WaveOps3<NT, KMAX, BC, RT>& w, const bf16_t* pa, uint32_t la, size_t tstride,
+                                               const bf16_t* pb, const uint32_t (&lb)[NT], int bstep, f32x4 (&acc)[RT][NT]) {
+  auto ld_a = [&](int chunk) {
+#pragma unroll
+    for (int s = chunk * BC; s < (chunk + 1) * BC; ++s)
+#pragma unroll
+        for (int r = 0; r < RT; ++r)
+          w.a[r][s] = kStream ? ld_bf16x8_stream(pa + r * tstride + s * kFrag + la) : ld_bf16x8(pa + r * tstride + s * kFrag + la);
+  };
+  auto mma = [&](int chunk, int buf) {
+#pragma unroll
+    for (int s = 0; s < BC; ++s)
+#pragma unroll
+        for (int ct = 0; ct < NT; ++ct)
+#pragma unroll
+          for (int r = 0; r < RT; ++r)
+            acc[r][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w.a[r][chunk * BC + s], w.b[buf][s][ct], acc[r][ct], 0,
+                                                                 0, 0);
+  };
+  issue_b3<0>(w, pb, lb, bstep);
+  ld_a(0);
+  __builtin_amdgcn_sched_barrier(0);
+  issue_b3<1>(w, pb, lb, bstep);
+  ld_a(1);
+  __builtin_amdgcn_sched_barrier(0);
+  issue_b3<2>(w, pb, lb, bstep);
+  ld_a(2);
+  ld_a(3);
+  __builtin_amdgcn_sched_barrier(0);
+  mma(0, 0);
+  __builtin_amdgcn_sched_barrier(0);
+  issue_b3<3>(w, pb, lb, bstep);
+  __builtin_amdgcn_sched_barrier(0);
+  mma(1, 1);
+  mma(2, 2);
+  mma(3, 0);
+}
+
+// The same for a burst of K steps whose operands all fit in registers.
+template <bool kStream, int K, int NT, int RT>
+__device__ __forceinline__ void wave_dot_short(const bf16_t* pa, uint32_t la, size_t tstride, const bf16_t* pb,
+                                               const uint32_t (&lb)[NT], int bstep, f32x4 (&acc)[RT][NT]) {
+  bf16x8 a[RT][K], b[K][NT];
+#pragma unroll
+  for (int s = 0; s < K; ++s) {
+#pragma unroll
+    for (int ct = 0; ct < NT; ++ct) b[s][ct] = ld_bf16x8(pb + s * bstep + lb[ct]);
+#pragma unroll
+    for (int r = 0; r < RT; ++r)
+      a[r][s] = kStream ? ld_bf16x8_stream(pa + r * tstride + s * kFrag + la)
+                        : ld_bf16x8(pa + r * tstride + s * kFrag + la);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int s = 0; s < K; ++s)
+#pragma unroll
+    for (int ct = 0; ct < NT; ++ct)
+#pragma unroll
+      for (int r = 0; r < RT; ++r)
+        acc[r][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[r][s], b[s][ct], acc[r][ct], 0, 0, 0);
+}
+
 // Sum the four waves' partial tiles into wave 0's registers (wave order).
 template <int RT, int NT>
 __device__ __forceinline__ void reduce_waves(f32x4 (&acc)[RT][NT], f32x4 (*red)[RT][NT][kWave], int wave,

@@ -184,7 +184,7 @@ __host__ __device__ inline size_t prologue_words(int T, int E) {
 // loads in flight together.  Probabilities go to P (LDS, row stride Es) and,
 // for the first workgroup, to probs (and the logits to logits when requested).
 template <int NQ, int NPASS>
-__device__ void rows_softmax(const LayerParams& p, float* P, int Es, bool first) {
+__device__ __forceinline__ void rows_softmax(const LayerParams& p, float* P, float* bl, int Es, bool first) {
   // E % 4 == 0 (checked by layer_fused_fits): a lane's pieces lie wholly in
   // or past the row, and pieces past it are masked, not branched around, so
   // all loads of a pass are issued before the first wait.
@@ -193,16 +193,12 @@ __device__ void rows_softmax(const LayerParams& p, float* P, int Es, bool first)
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int sl = lane & 7;
   const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
-  f32x4 b[NV];
-#pragma unroll
-  for (int i = 0; i < NV; ++i) b[i] = zero4;
+  // the bias waits in LDS (bl), not in registers: they hold the loads in flight
+  constexpr int kBiasPer = 256 * NQ / kThreads;
+  float bv[kBiasPer];
   if (p.bias) {
 #pragma unroll
-    for (int i = 0; i < NV; ++i) {
-      const int e0 = 4 * (sl + 8 * i);
-      const f32x4 v = *reinterpret_cast<const f32x4*>(p.bias + min(e0, E - 4));
-      b[i] = e0 < E ? v : zero4;
-    }
+    for (int i = 0; i < kBiasPer; ++i) bv[i] = p.bias[min(static_cast<int>(threadIdx.x) + i * kThreads, E - 1)];
   }
 #pragma unroll
   for (int pass = 0; pass < NPASS; ++pass) {
@@ -220,6 +216,13 @@ __device__ void rows_softmax(const LayerParams& p, float* P, int Es, bool first)
 #pragma unroll
       for (int i = 0; i < NV; ++i) zs[h - 1][i] = *reinterpret_cast<const f32x4*>(sh + min(4 * (sl + 8 * i), E - 4));
     }
+    __builtin_amdgcn_sched_barrier(0);
+    if (pass == 0 && p.bias) {  // uniform
+#pragma unroll
+      for (int i = 0; i < kBiasPer; ++i) bl[threadIdx.x + i * kThreads] = bv[i];
+      __syncthreads();
+    }
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int h = 1; h < NS; ++h)  // slice order
 #pragma unroll
@@ -229,7 +232,7 @@ __device__ void rows_softmax(const LayerParams& p, float* P, int Es, bool first)
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
       const bool in = 4 * (sl + 8 * i) < E;
-      z[i] += b[i];
+      if (p.bias) z[i] += *reinterpret_cast<const f32x4*>(bl + 4 * (sl + 8 * i));
 #pragma unroll
       for (int c = 0; c < 4; ++c) m = fmaxf(m, in ? z[i][c] : -INFINITY);
     }
@@ -287,25 +290,63 @@ __device__ void rows_softmax(const LayerParams& p, float* P, int Es, bool first)
 template <int NT>
 constexpr int kRTof = NT <= 2 ? 2 : 1;
 
+// acc += the wave's K-slice of RT gate/up tiles over NT token tiles: weights
+// at pa + la, tokens at pb + lb[ct] (uniform base + lane offset).  Slices of
+// whole bursts (16 K-steps per wave: H a multiple of 2048; else 8, 10, 6 or 7: of
+// 1024, 1280, 768 or 1792; or the whole of 256 or 512) run straight-line, tokens
+// and weights issued alternately.  Measured, us per layer of the decode
+// shape, against bursts with two token buffers: 28.4 -> 27.9, at hidden 4096
+// 50.7 -> 48.1, at 1024 24.4 -> 23.7.  Loading the first token chunk or two
+// before the routing spilled them (30.5, 34.7).
+template <int NT, int RT>
+__device__ __forceinline__ void gateup_dot(const bf16_t* pa, uint32_t la, size_t tstride, const bf16_t* pb,
+                                           const uint32_t (&lb)[NT], int bstep, int steps, f32x4 (&acc)[RT][NT]) {
+  if constexpr (NT <= 2) {
+    if (steps % 16 == 0) {
+      fdev::WaveOps3<NT, 16, 4, RT> w;
+      for (int sc = 0; sc < steps; sc += 16)
+        fdev::wave_dot_burst<true>(w, pa + sc * kFrag, la, tstride, pb + sc * bstep, lb, bstep, acc);
+      return;
+    }
+#define DMOE_SHORT(K_)                                                                                            \
+  if (steps % K_ == 0) {                                                                                          \
+    for (int sc = 0; sc < steps; sc += K_)                                                                        \
+      fdev::wave_dot_short<true, K_>(pa + sc * kFrag, la, tstride, pb + sc * bstep, lb, bstep, acc);              \
+    return;                                                                                                       \
+  }
+    DMOE_SHORT(8)
+    DMOE_SHORT(10)
+    DMOE_SHORT(6)
+    DMOE_SHORT(7)
+    if (steps <= 4) {  // H of 256 or 512
+      DMOE_SHORT(4)
+      DMOE_SHORT(2)
+    }
+#undef DMOE_SHORT
+  }
+  const bf16_t* pl[NT];
+#pragma unroll
+  for (int ct = 0; ct < NT; ++ct) pl[ct] = pb + lb[ct];
+  fdev::WaveOps<NT, 16, 4, RT> w;
+  fdev::wave_dot<true>(w, pa + la, tstride, pl, bstep, steps, acc, false);
+}
+
 // The shared expert's gate/up tiles over all T tokens (chunk-major x).
 template <int NT>
 __device__ void shared_gateup_tiles(const LayerParams& p, int it0, f32x4 (*red)[kRTof<NT>][NT][kWave]) {
   constexpr int kRT = kRTof<NT>;
   const int T = p.T, H = p.H;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, q = lane >> 4, c = lane & 15;
+  const int uw = __builtin_amdgcn_readfirstlane(wave);
   const int ksteps = H >> 5, steps = ksteps >> 2;
-  const bf16_t* pa = p.ws13 + (static_cast<size_t>(it0) * ksteps + wave * steps) * kFrag + lane * 8;
-  const int chunk0 = wave * steps * 4 + q;
-  const bf16_t* pb[NT];
+  const bf16_t* pa = p.ws13 + (static_cast<size_t>(it0) * ksteps + uw * steps) * kFrag;
+  const bf16_t* pb = p.xk + static_cast<size_t>(uw * steps * 4) * T * 8;
+  uint32_t lb[NT];
 #pragma unroll
-  for (int ct = 0; ct < NT; ++ct) {
-    const int tok = min(ct * kTok + c, T - 1);
-    pb[ct] = p.xk + (static_cast<size_t>(chunk0) * T + tok) * 8;
-  }
+  for (int ct = 0; ct < NT; ++ct) lb[ct] = (q * T + min(ct * kTok + c, T - 1)) * 8;
   f32x4 acc[kRT][NT];
   fdev::zero(acc);
-  fdev::WaveOps<NT, 16, 4, kRT> w;
-  fdev::wave_dot<true>(w, pa, static_cast<size_t>(ksteps) * kFrag, pb, 32 * T, steps, acc, false);
+  gateup_dot<NT, kRT>(pa, lane * 8, static_cast<size_t>(ksteps) * kFrag, pb, lb, 32 * T, steps, acc);
   fdev::reduce_waves(acc, red, wave, lane);
   if (wave != 0) return;
 #pragma unroll
@@ -328,6 +369,7 @@ __global__ __launch_bounds__(kThreads, 2) void layer_route_gateup_kernel(LayerPa
   __shared__ float wslot[NT * kTok];
   __shared__ f32x4 red[kWaves - 1][kRTof<NT>][NT][kWave];
   __shared__ dev::BlockTopkLds tk;
+  __shared__ __align__(16) float bl[256 * NQ];
   constexpr int kRT = kRTof<NT>;
   const int T = p.T, E = p.E, k = p.k;
   const int Es = dev::pad4(E);
@@ -342,9 +384,16 @@ __global__ __launch_bounds__(kThreads, 2) void layer_route_gateup_kernel(LayerPa
   float* P = lds;
   float* S = lds + static_cast<size_t>(T) * Es;
 
+  const int H = p.H, q = lane >> 4, c = lane & 15;
+  const int ksteps = H >> 5, steps = ksteps >> 2;
+  const int uw = __builtin_amdgcn_readfirstlane(wave);
+  const bf16_t* pb = p.xk + static_cast<size_t>(uw * steps * 4) * T * 8;
+  uint32_t lb[NT];
+#pragma unroll
+  for (int ct = 0; ct < NT; ++ct) lb[ct] = (q * T + min(ct * kTok + c, T - 1)) * 8;
   // 1. softmax of each token row: wave w owns rows w, w + 4, ..., all of
   //    whose loads are issued at once (one memory round trip)
-  rows_softmax<NQ, (NT * kTok + 8 * kWaves - 1) / (8 * kWaves)>(p, P, Es, first);
+  rows_softmax<NQ, (NT * kTok + 8 * kWaves - 1) / (8 * kWaves)>(p, P, bl, Es, first);
   __syncthreads();
 
   // 2. block means in token order, 3. top-(k+1) by one wave
@@ -368,21 +417,11 @@ __global__ __launch_bounds__(kThreads, 2) void layer_route_gateup_kernel(LayerPa
   __syncthreads();
 
   // 5. packed tile `it` of expert sel[j]'s gate/up over all tokens
-  const int H = p.H, q = lane >> 4, c = lane & 15;
-  const int ksteps = H >> 5, steps = ksteps >> 2;
-  const bf16_t* W = p.w13 + static_cast<size_t>(sel[j]) * 2 * p.I * H;
-  const bf16_t* pa = W + (static_cast<size_t>(it) * ksteps + wave * steps) * kFrag + lane * 8;
-  const int chunk0 = wave * steps * 4 + q;
-  const bf16_t* pb[NT];
-#pragma unroll
-  for (int ct = 0; ct < NT; ++ct) {
-    const int tok = min(ct * kTok + c, T - 1);
-    pb[ct] = p.xk + (static_cast<size_t>(chunk0) * T + tok) * 8;
-  }
+  const bf16_t* W = p.w13 + static_cast<size_t>(__builtin_amdgcn_readfirstlane(sel[j])) * 2 * p.I * H;
+  const bf16_t* pa = W + (static_cast<size_t>(it) * ksteps + uw * steps) * kFrag;
   f32x4 acc[kRT][NT];
   fdev::zero(acc);
-  fdev::WaveOps<NT, 16, 4, kRT> w;
-  fdev::wave_dot<true>(w, pa, static_cast<size_t>(ksteps) * kFrag, pb, 32 * T, steps, acc, false);
+  gateup_dot<NT, kRT>(pa, lane * 8, static_cast<size_t>(ksteps) * kFrag, pb, lb, 32 * T, steps, acc);
 
   // 6. the routing outputs (workgroup (0, 0), while the other workgroups
   //    stream): the selection, gap, every token's combine weights (its

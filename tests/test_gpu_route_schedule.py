@@ -1,0 +1,61 @@
+"""One-call routing at the sizes where its launches change, bit for bit against
+the separate entry points: schedules of one round of entries and more
+(512), blocks below and above the LDS limit of a routing workgroup, ragged
+last workgroups, odd expert counts.  Three eager calls on one set of buffers
+and three replays of a captured graph, with other work between them, each on
+other hidden states; the work items are compared too."""
+import pytest
+import torch
+
+from dmoe_synth import get_config, make_inputs
+from paper_2605_30876_amd.layer import MoELayer
+
+pytestmark = pytest.mark.gpu
+
+TOKEN = [dict(E=256, k=8, NB=1, bs=32), dict(E=256, k=8, NB=2, bs=32), dict(E=256, k=8, NB=5, bs=13), dict(E=257, k=8, NB=1, bs=32), dict(E=48, k=4, NB=1, bs=64),
+         dict(E=48, k=5, NB=4, bs=13), dict(E=16, k=1, NB=7, bs=3), dict(E=9, k=9, NB=3, bs=9)]
+BLOCK = [dict(E=64, k=8, NB=2, bs=5), dict(E=64, k=8, NB=64, bs=4), dict(E=64, k=8, NB=65, bs=4),
+         dict(E=256, k=8, NB=3, bs=64), dict(E=256, k=8, NB=2, bs=72), dict(E=256, k=8, NB=2, bs=80),
+         dict(E=300, k=17, NB=5, bs=24), dict(E=512, k=3, NB=6, bs=9)]
+
+
+def _snapshot(m, routing, rows):
+    s = m.sched
+    n, nw = int(s.n_unique[0]), int(s.n_work[0])
+    return [m.probs, m.combine_w, m.experts(routing), m.gaps(routing), s.n_unique[:1], s.n_work[:1], s.unique[:n],
+            s.offsets[:n + 1], s.row_token[:rows], s.row_slot[:rows], s.work[:nw]]
+
+
+@pytest.mark.parametrize("routing,over", [(r, o) for r in ("token", "topp") for o in TOKEN] +
+                         [("block", o) for o in BLOCK])
+def test_routing_launch_sizes(gpu_lib, routing, over):
+    cfg = get_config("small_bf16").with_(name="rs", H=256, I=128, I_s=0, **over)
+    print("case", routing, over, flush=True)
+    mk = lambda: MoELayer(cfg.H, cfg.E, cfg.I, cfg.I_s, cfg.k, cfg.NB, cfg.bs, device="cuda")  # noqa: E731
+    fused, chain = mk(), mk()
+    rows = cfg.T * cfg.k
+    ds = [make_inputs(cfg, seed=s, device="cuda") for s in range(4)]
+    wr = ds[0]["w_router"]
+    x = ds[0]["x"].clone()
+
+    def check():
+        torch.cuda.synchronize()
+        chain.route(x, wr, None, routing, fused=False)
+        torch.cuda.synchronize()
+        for i, (a, b) in enumerate(zip(_snapshot(fused, routing, rows), _snapshot(chain, routing, rows))):
+            assert torch.equal(a, b), i
+
+    for t in (fused.sched.n_work, fused.sched.work, fused.sched.row_token):
+        t.fill_(-7)
+    for d in ds[:3]:
+        x.copy_(d["x"])
+        fused.route(x, wr, None, routing, fused=True)
+        check()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        fused.route(x, wr, None, routing, fused=True)
+    for d in (ds[3], ds[1], ds[2]):
+        x.copy_(d["x"])
+        fused.sched.n_work.fill_(3)
+        g.replay()
+        check()
