@@ -184,7 +184,7 @@ __host__ __device__ inline size_t prologue_words(int T, int E) {
 // loads in flight together.  Probabilities go to P (LDS, row stride Es) and,
 // for the first workgroup, to probs (and the logits to logits when requested).
 template <int NQ, int NPASS>
-__device__ __forceinline__ void rows_softmax(const LayerParams& p, float* P, float* bl, int Es, bool first) {
+__device__ void rows_softmax(const LayerParams& p, float* P, int Es, bool first) {
   // E % 4 == 0 (checked by layer_fused_fits): a lane's pieces lie wholly in
   // or past the row, and pieces past it are masked, not branched around, so
   // all loads of a pass are issued before the first wait.
@@ -193,12 +193,16 @@ __device__ __forceinline__ void rows_softmax(const LayerParams& p, float* P, flo
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int sl = lane & 7;
   const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
-  // the bias waits in LDS (bl), not in registers: they hold the loads in flight
-  constexpr int kBiasPer = 256 * NQ / kThreads;
-  float bv[kBiasPer];
+  f32x4 b[NV];
+#pragma unroll
+  for (int i = 0; i < NV; ++i) b[i] = zero4;
   if (p.bias) {
 #pragma unroll
-    for (int i = 0; i < kBiasPer; ++i) bv[i] = p.bias[min(static_cast<int>(threadIdx.x) + i * kThreads, E - 1)];
+    for (int i = 0; i < NV; ++i) {
+      const int e0 = 4 * (sl + 8 * i);
+      const f32x4 v = *reinterpret_cast<const f32x4*>(p.bias + min(e0, E - 4));
+      b[i] = e0 < E ? v : zero4;
+    }
   }
 #pragma unroll
   for (int pass = 0; pass < NPASS; ++pass) {
@@ -216,13 +220,6 @@ __device__ __forceinline__ void rows_softmax(const LayerParams& p, float* P, flo
 #pragma unroll
       for (int i = 0; i < NV; ++i) zs[h - 1][i] = *reinterpret_cast<const f32x4*>(sh + min(4 * (sl + 8 * i), E - 4));
     }
-    __builtin_amdgcn_sched_barrier(0);
-    if (pass == 0 && p.bias) {  // uniform
-#pragma unroll
-      for (int i = 0; i < kBiasPer; ++i) bl[threadIdx.x + i * kThreads] = bv[i];
-      __syncthreads();
-    }
-    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int h = 1; h < NS; ++h)  // slice order
 #pragma unroll
@@ -232,7 +229,7 @@ __device__ __forceinline__ void rows_softmax(const LayerParams& p, float* P, flo
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
       const bool in = 4 * (sl + 8 * i) < E;
-      if (p.bias) z[i] += *reinterpret_cast<const f32x4*>(bl + 4 * (sl + 8 * i));
+      z[i] += b[i];
 #pragma unroll
       for (int c = 0; c < 4; ++c) m = fmaxf(m, in ? z[i][c] : -INFINITY);
     }
@@ -369,7 +366,6 @@ __global__ __launch_bounds__(kThreads, 2) void layer_route_gateup_kernel(LayerPa
   __shared__ float wslot[NT * kTok];
   __shared__ f32x4 red[kWaves - 1][kRTof<NT>][NT][kWave];
   __shared__ dev::BlockTopkLds tk;
-  __shared__ __align__(16) float bl[256 * NQ];
   constexpr int kRT = kRTof<NT>;
   const int T = p.T, E = p.E, k = p.k;
   const int Es = dev::pad4(E);
@@ -393,7 +389,7 @@ __global__ __launch_bounds__(kThreads, 2) void layer_route_gateup_kernel(LayerPa
   for (int ct = 0; ct < NT; ++ct) lb[ct] = (q * T + min(ct * kTok + c, T - 1)) * 8;
   // 1. softmax of each token row: wave w owns rows w, w + 4, ..., all of
   //    whose loads are issued at once (one memory round trip)
-  rows_softmax<NQ, (NT * kTok + 8 * kWaves - 1) / (8 * kWaves)>(p, P, bl, Es, first);
+  rows_softmax<NQ, (NT * kTok + 8 * kWaves - 1) / (8 * kWaves)>(p, P, Es, first);
   __syncthreads();
 
   // 2. block means in token order, 3. top-(k+1) by one wave
