@@ -428,8 +428,9 @@ __device__ __forceinline__ void tile_body(const FfnParams& p, const Group& g, in
       if (kFrags % kWaves == 0 || f < kFrags) dma16(pb[i] + st * kSteps * bstep, &d[f / kCt][f % kCt][0]);
     }
   };
-  // memory operations of one stage's loads; a wave that has a fragment less
-  // to load only waits for that much less of its own weights
+  // Memory operations of one stage's loads.  (Where kWaves does not divide
+  // kFrags, a wave loads one fragment of a stage or none; a wave without one
+  // has nothing in LDS to wait for.)
   constexpr int kIssued = kFragWave + kSteps * kRowTiles;
 
   load_b(0, lds.s0);
@@ -443,12 +444,18 @@ __device__ __forceinline__ void tile_body(const FfnParams& p, const Group& g, in
   __builtin_amdgcn_sched_barrier(0);
   // stage st uses ring slot and LDS buffer R = st % 3 (compile-time indexes:
   // three stages per trip).  The buffer it refills was last read in stage
-  // st - 1, before the barrier that ended it.
-  auto run_stage = [&](auto slot, int st, Stage& cur, Stage& fill) {
-    constexpr int R = decltype(slot)::value;
-    const int nx = min(st + 2, nstages - 1);  // past the end: the last stage again, never used
-    load_b(nx, fill);
-    load_a(nx, a_reg[(R + 2) % 3]);
+  // st - 1, before the barrier that ended it.  A stage of the loop (kFull)
+  // loads stage st + 2 and waits for all but those loads, whatever their
+  // order: stage st + 1 has arrived.  The one or two stages after the loop
+  // load nothing; the first waits for everything, the last for nothing.
+  enum { kFull, kDrain, kLast };
+  auto run_stage = [&](auto slot, auto kind, int st, Stage& cur, Stage& fill) {
+    constexpr int R = decltype(slot)::value, kKind = decltype(kind)::value;
+    if constexpr (kKind == kFull) {
+      const int nx = min(st + 2, nstages - 1);  // past the end: the last stage again, never used
+      load_b(nx, fill);
+      load_a(nx, a_reg[(R + 2) % 3]);
+    }
     __builtin_amdgcn_sched_barrier(0);
     // token tile by token tile: the next tile's fragments are read from LDS
     // while this tile's matrix instructions run
@@ -469,18 +476,25 @@ __device__ __forceinline__ void tile_body(const FfnParams& p, const Group& g, in
           acc[m][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a_reg[R][s][m], b[ct & 1][s], acc[m][ct], 0, 0, 0);
     }
     __builtin_amdgcn_sched_barrier(0);
-    wait_vm<kIssued>();  // all but this stage's loads: stage st + 1 has arrived
+    if constexpr (kKind == kLast) return;
+    wait_vm<kKind == kFull ? kIssued : 0>();
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
   };
+  constexpr std::integral_constant<int, 0> r0;
+  constexpr std::integral_constant<int, 1> r1;
+  constexpr std::integral_constant<int, 2> r2;
+  constexpr std::integral_constant<int, kFull> full;
+  constexpr std::integral_constant<int, kDrain> drain;
+  constexpr std::integral_constant<int, kLast> last;
   int st = 0;
   for (; st + 3 <= nstages; st += 3) {
-    run_stage(std::integral_constant<int, 0>{}, st, lds.s0, lds.s2);
-    run_stage(std::integral_constant<int, 1>{}, st + 1, lds.s1, lds.s0);
-    run_stage(std::integral_constant<int, 2>{}, st + 2, lds.s2, lds.s1);
+    run_stage(r0, full, st, lds.s0, lds.s2);
+    run_stage(r1, full, st + 1, lds.s1, lds.s0);
+    run_stage(r2, full, st + 2, lds.s2, lds.s1);
   }
-  if (st < nstages) run_stage(std::integral_constant<int, 0>{}, st, lds.s0, lds.s2);
-  if (st + 1 < nstages) run_stage(std::integral_constant<int, 1>{}, st + 1, lds.s1, lds.s0);
+  if (st < nstages) run_stage(r0, drain, st, lds.s0, lds.s2);
+  if (st + 1 < nstages) run_stage(r1, last, st + 1, lds.s1, lds.s0);
   wait_vm<0>();  // the loads into LDS end before the buffers are reused or the workgroup ends
 
   if constexpr (kGateUp) {

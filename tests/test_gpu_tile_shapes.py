@@ -29,3 +29,15 @@ def test_wide_tile_workgroups(gpu_lib, name, routing, slots):
     d = {k: (None if v is None else v.cuda()) for k, v in make_inputs(cfg, seed=4).items()}
     m = MoELayer(cfg.H, cfg.E, cfg.I, cfg.I_s, cfg.k, cfg.NB, cfg.bs, device="cuda", slot_format=slots)
     run_and_check(cfg, d, routing, m)
+
+
+@pytest.mark.parametrize("n", [128, 256, 384, 512, 640])
+@pytest.mark.parametrize("nb", [16, 64])
+def test_ring_ends(gpu_lib, n, nb):
+    """Both products of 2 to 10 two-step stages (4 to 20 one-step ones where
+    the grid takes wide workgroups): every remainder of the three-stage trips."""
+    cfg = get_config("small_bf16").with_(name="ring", H=n, E=64, I=n, I_s=n, k=8, NB=nb, bs=48)
+    print("case", n, nb, flush=True)
+    d = {k: (None if v is None else v.cuda()) for k, v in make_inputs(cfg, seed=8).items()}
+    m = MoELayer(cfg.H, cfg.E, cfg.I, cfg.I_s, cfg.k, cfg.NB, cfg.bs, device="cuda")
+    run_and_check(cfg, d, "block", m, sample_tokens=list(range(0, cfg.T, 7)))
