@@ -671,8 +671,13 @@ int pick_ntiles(int T, int k, int max_work) {
 // how much is in flight for workgroups of tens of KB: the one-tile down
 // kernel at bursts of four K-steps (intermediate 512 in one) holds five per
 // CU where eight-step bursts held three (32 tokens of the decode layer, token
-// routing 186 -> 179 us per layer, Top-P 106 -> 102; two bursts at
-// intermediate 1024 235 -> 234; forced to six per CU 201); the two-tile
+// routing 186 -> 179 us per layer, Top-P 106 -> 102; forced to six per CU
+// 201).  Slices of five to eight steps keep the eight-step burst: only a
+// one-burst slice stays in registers across the 16-row passes of an item,
+// and an expert with many rows would read it once per pass (token routing of
+// 192 tokens over 128 Zipf-biased experts of intermediate 1024: 204 us per
+// layer, in two bursts of four 256; 64 tokens 126 against 140, intermediate
+// 768 107 against 117; without the bias equal to 3 %).  The two-tile
 // gate/up kernel at eight steps holds four (five blocks of 24 tokens over 48
 // experts 47.2 -> 45.1, two blocks of 32 of the decode layer 56.5 -> 55.5).
 // Other gate/up bursts at one token tile measured within 1.5 % (four and
@@ -682,6 +687,7 @@ struct Shape;
 template <>
 struct Shape<1> {
   static constexpr int kGuMax = 16, kGuChunk = 4, kGuWaves = 2, kDnMax = 4, kDnChunk = 4, kDnWaves = 4;
+  static constexpr int kDnLong = 8, kDnLongWaves = 3;  // down slices longer than kDnMax
   static constexpr int kGuRows = 2, kDnRows = 2;
   static constexpr bool kSharedFirst = true;
 };
@@ -719,8 +725,16 @@ hipError_t launch_bf16(const FfnParams& p, int ldh, int groups, hipStream_t s) {
         <<<grid, kThreads, 0, s>>>(p);
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
+  const dim3 grid_dn(p.H / (16 * S::kDnRows), groups, passes);
+  if constexpr (NT == 1) {
+    if (ldh / 128 > S::kDnMax) {
+      ffn_down_bf16_kernel<NT, S::kDnLong, S::kDnChunk, S::kDnLongWaves, S::kSharedFirst, S::kDnRows>
+          <<<grid_dn, kThreads, 0, s>>>(p);
+      return hipGetLastError();
+    }
+  }
   ffn_down_bf16_kernel<NT, S::kDnMax, S::kDnChunk, S::kDnWaves, S::kSharedFirst, S::kDnRows>
-      <<<dim3(p.H / (16 * S::kDnRows), groups, passes), kThreads, 0, s>>>(p);
+      <<<grid_dn, kThreads, 0, s>>>(p);
   return hipGetLastError();
 }
 
@@ -771,7 +785,6 @@ hipError_t launch_tiles(const FfnParams& p, int ldh, int items, long rows, hipSt
 }
 
 constexpr int kPassRows = 16;    // token rows of one decode-kernel pass
-constexpr int kSliceSteps = 16;  // K-steps of a wave's gate/up slice beyond which a schedule takes the tile kernels
 
 bool use_tile_kernels(int T, int k, int max_work, int items, int ldh) {
   return rows_per_item(T, k, max_work) >= 32 && static_cast<long>(ldh / 32) * items >= 512;
@@ -817,7 +830,7 @@ hipError_t launch_ffn(const FfnArgs& a, dmoe_dtype dt, hipStream_t s) {
         // faster too (512 tokens over 256 experts at hidden 2048: token
         // routing 321 -> 283 us, Top-P 317 -> 306; 256 tokens and fewer
         // favour the decode kernels).
-        const bool multi_burst = a.H / 128 > kSliceSteps || ldh / 128 > kSliceSteps / 2;
+        const bool multi_burst = a.H / 128 > Shape<1>::kGuMax || ldh / 128 > Shape<1>::kDnLong;
         const bool pass_per_expert = static_cast<long>(a.T) * a.k >= static_cast<long>(kPassRows) * a.E;
         if (a.T > kPassRows && (multi_burst || pass_per_expert)) {
           return launch_tiles(p, ldh, items, rows_per_item(a.T, a.k, a.max_work), s);
