@@ -348,10 +348,12 @@ size_t dmoe_ffn_workspace_size(int T, int I, int I_s, int k, dmoe_dtype dt);
  *   slot_out[t][j][:] = W_down[e] h
  * and, when the shared expert is present (ws13 != NULL), for every token t:
  *   shared_out[t][:] = Ws_down (silu(Ws_gate x_t) * (Ws_up x_t))
- * Each selected expert's weights are streamed once per work item: an
+ * Each selected expert's weights are streamed about once per work item: an
  * expert's rows are cut into items of at most DMOE_WORK_ROWS, and an expert
  * with more rows than that (a popular expert, or the shared expert over more
- * than DMOE_WORK_ROWS tokens) is streamed once per item.
+ * than DMOE_WORK_ROWS tokens) is streamed once per item.  (Where several
+ * workgroups share an item's rows, or one runs them in passes over weights
+ * too long for its registers, the later reads mostly come from a cache.)
  * x_chunked: the hidden states x [T][H] in the chunk-major layout above.
  * x: the same hidden states row-major [T][H], optional (NULL: not used).
  * With it, bf16 rows whose tokens are not consecutive (token-level routing)

@@ -13,7 +13,7 @@
 // faster for block-routed decode steps).  A decode workgroup owns one or two
 // 16-row weight tiles of one item, streams them from HBM and applies them to
 // the item's rows (tokens); a tile workgroup owns 64 or 128 weight rows and
-// up to 128 tokens.  Each selected expert's weights are read once per forward
+// up to 128 tokens.  Each selected expert's weights are read from memory once per forward
 // per piece of its rows.
 //
 // bf16 path (matrix cores, v_mfma_f32_16x16x32_bf16, fp32 accumulation):
@@ -116,22 +116,12 @@ __device__ __forceinline__ int slot_exponent(const FfnParams& p, const f32x4& v)
 
 using namespace fdev;  // the wave-level operand helpers of ffn_dev.h
 
-// Occupancy floors (waves per SIMD) for the two-tile variants, which serve
-// block-routed decode steps: 3 (gate/up and down) keep every workgroup of
-// such a launch resident at once instead of leaving a second partial round.
-// grid (ldh / (8 RT), groups, passes): packed gate/up tiles it .. it + RT - 1, tile
-// `it` = 8 intermediate units.
-// Wave w reduces over hidden chunks [w*H/32, (w+1)*H/32) (K-steps
-// [w*H/128, (w+1)*H/128)).
-template <int NT, int KMAX, int BC, int MINW, bool kSharedFirst, int RT>
-__global__ __launch_bounds__(kThreads, MINW) void ffn_gateup_bf16_kernel(FfnParams p) {
-  Group g;
-  if (!decode_item<kSharedFirst>(blockIdx.y, p.shared_items, p.max_work, p.n_work, p.work, p.row_token, p.T,
-                                 p.Tk, p.E, g))
-    return;
-  const int Iw = g.expert >= 0 ? p.I : p.I_s;
-  const int it = blockIdx.x * RT;  // first of the RT packed tiles (Iw / 8 is a multiple of 16)
-  if (it * 8 >= Iw) return;
+// One gate/up workgroup's rows [pz, pend) of the item: packed tiles it ..
+// it + RT - 1 over them.  Wave w reduces over hidden chunks
+// [w*H/32, (w+1)*H/32) (K-steps [w*H/128, (w+1)*H/128)).
+template <bool kStream, int NT, int KMAX, int BC, int RT>
+__device__ __forceinline__ void gateup_rows(const FfnParams& p, const Group& g, int it, int pz, int pend,
+                                            f32x4 (*red)[RT][NT][kWave]) {
   const int H = p.H;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int q = lane >> 4, c = lane & 15;
@@ -141,24 +131,15 @@ __global__ __launch_bounds__(kThreads, MINW) void ffn_gateup_bf16_kernel(FfnPara
   const size_t tstride = static_cast<size_t>(ksteps) * kFrag;  // next packed tile
   const int bstep = 32 * p.T;  // 4 chunks of T tokens per K-step
   const int chunk0 = wave * steps * 4 + q;
-
-  // One token tile: all passes here, over weights held in registers.  More:
-  // one pass per workgroup (grid z; these launches are small, and the passes
-  // of an item of many rows, the shared expert's above all, were their long
-  // pole: five blocks of 24 tokens over 48 experts 50.6 -> 47.8 us per layer).
-  constexpr bool kPassZ = NT > 1;
-  const int pz = kPassZ ? blockIdx.z * 16 * NT : 0, pend = kPassZ ? min(g.n, pz + 16 * NT) : g.n;
-  __shared__ f32x4 red[3][RT][NT][kWave];
   WaveOps<NT, KMAX, BC, RT> w;  // a one-burst weight slice stays here across passes
   // At two token tiles (items of whole blocks) a one-burst slice is loaded
   // before the token rows are known: the weights wait only for the work
   // item, not for its row list and then x.  With one token tile (many small
   // items) the token fragments going first measured faster.
   bool a_held = false;
-  if (kPassZ && pz >= g.n) return;
   if constexpr (NT == 2) {
     if (steps <= KMAX) {
-      issue_a<true>(w, pa, tstride, steps);
+      issue_a<kStream>(w, pa, tstride, steps);
       a_held = true;
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -179,7 +160,7 @@ __global__ __launch_bounds__(kThreads, MINW) void ffn_gateup_bf16_kernel(FfnPara
                         : p.xk + (static_cast<size_t>(chunk0) * p.T + tok[ct]) * 8;
     f32x4 acc[RT][NT];
     zero(acc);
-    wave_dot<true>(w, pa, tstride, pb, gathered ? 32 : bstep, steps, acc, a_held || (p0 > pz && steps <= KMAX));
+    wave_dot<kStream>(w, pa, tstride, pb, gathered ? 32 : bstep, steps, acc, a_held || (p0 > pz && steps <= KMAX));
     reduce_waves(acc, red, wave, lane);
     if (wave == 0) {
 #pragma unroll
@@ -201,17 +182,50 @@ __global__ __launch_bounds__(kThreads, MINW) void ffn_gateup_bf16_kernel(FfnPara
   }
 }
 
-// grid (H / (16 RT), groups, passes): packed down tiles jt .. jt + RT - 1, tile `jt`
-// = 16 output features.
+// One token tile: a workgroup takes all 16-row passes of its item, over
+// weights held in registers.  More: one pass of 16*NT rows per workgroup
+// (these launches are small, and the passes of an item of many rows, the
+// shared expert's above all, were their long pole: five blocks of 24 tokens
+// over 48 experts 50.6 -> 47.8 us per layer).  Grid (tiles, passes, items): an
+// item's passes are dispatched one after the other, tiles a multiple of 8, so
+// that the passes of one tile meet on one XCD, and load their weights
+// plainly: the later ones find them in that XCD's L2.  Hidden 2048, 128
+// experts of intermediate 512, top-8, Zipf-biased router, us per layer, one
+// workgroup running all passes over held weights / passes in the slowest grid
+// dimension, non-temporal / these: three blocks of 32 tokens 59.4 / 68.6 /
+// 54.8, six of 24 74.0 / 89.0 / 71.4; unbiased 71.8 / 69.5 / 64.7 and 99.5 /
+// 99.5 / 90.3.  (Both load types in one body spilled: 128 B a lane, 61.8 us
+// for two blocks of 32 against 52.6.)
+// Packed gate/up tile `it` = 8 intermediate units.
 template <int NT, int KMAX, int BC, int MINW, bool kSharedFirst, int RT>
-__global__ __launch_bounds__(kThreads, MINW) void ffn_down_bf16_kernel(FfnParams p) {
+__global__ __launch_bounds__(kThreads, MINW) void ffn_gateup_bf16_kernel(FfnParams p) {
   Group g;
-  if (!decode_item<kSharedFirst>(blockIdx.y, p.shared_items, p.max_work, p.n_work, p.work, p.row_token, p.T,
+  if (!decode_item<kSharedFirst>(blockIdx.z, p.shared_items, p.max_work, p.n_work, p.work, p.row_token, p.T,
                                  p.Tk, p.E, g))
     return;
+  const int Iw = g.expert >= 0 ? p.I : p.I_s;
+  const int it = blockIdx.x * RT;  // first of the RT packed tiles (Iw / 8 is a multiple of 16)
+  if (it * 8 >= Iw) return;
+  __shared__ f32x4 red[3][RT][NT][kWave];
+  if constexpr (NT == 1) {
+    gateup_rows<true, NT, KMAX, BC, RT>(p, g, it, 0, g.n, red);
+  } else {
+    const int pz = blockIdx.y * 16 * NT;
+    if (pz >= g.n) return;
+    if (g.n > 16 * NT)
+      gateup_rows<false, NT, KMAX, BC, RT>(p, g, it, pz, min(g.n, pz + 16 * NT), red);
+    else
+      gateup_rows<true, NT, KMAX, BC, RT>(p, g, it, 0, g.n, red);
+  }
+}
+
+// The same for the down projection: packed tiles jt .. jt + RT - 1, tile `jt`
+// = 16 output features.
+template <bool kStream, int NT, int KMAX, int BC, int RT>
+__device__ __forceinline__ void down_rows(const FfnParams& p, const Group& g, int jt, int pz, int pend,
+                                          f32x4 (*red)[RT][NT][kWave]) {
   const int Kd = g.expert >= 0 ? p.I : p.I_s;
   const int H = p.H;
-  const int jt = blockIdx.x * RT;  // first of the RT packed tiles (H / 16 is a multiple of 8)
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int q = lane >> 4, c = lane & 15;
   const int ksteps = Kd >> 5, steps = ksteps >> 2;
@@ -221,10 +235,7 @@ __global__ __launch_bounds__(kThreads, MINW) void ffn_down_bf16_kernel(FfnParams
   const int bstep = 32 * p.R;
   const int chunk0 = wave * steps * 4 + q;
 
-  __shared__ f32x4 red[3][RT][NT][kWave];
   WaveOps<NT, KMAX, BC, RT> w;  // a one-burst weight slice stays here across passes
-  constexpr bool kPassZ = NT > 1;
-  const int pz = kPassZ ? blockIdx.z * 16 * NT : 0, pend = kPassZ ? min(g.n, pz + 16 * NT) : g.n;
   for (int p0 = pz; p0 < pend; p0 += 16 * NT) {
     const bf16_t* pb[NT];
 #pragma unroll
@@ -234,7 +245,7 @@ __global__ __launch_bounds__(kThreads, MINW) void ffn_down_bf16_kernel(FfnParams
     }
     f32x4 acc[RT][NT];
     zero(acc);
-    wave_dot<true>(w, pa, tstride, pb, bstep, steps, acc, p0 > pz && steps <= KMAX);
+    wave_dot<kStream>(w, pa, tstride, pb, bstep, steps, acc, p0 > pz && steps <= KMAX);
     reduce_waves(acc, red, wave, lane);
     if (wave == 0) {
 #pragma unroll
@@ -256,6 +267,27 @@ __global__ __launch_bounds__(kThreads, MINW) void ffn_down_bf16_kernel(FfnParams
       }
     }
     __syncthreads();
+  }
+}
+
+template <int NT, int KMAX, int BC, int MINW, bool kSharedFirst, int RT>
+__global__ __launch_bounds__(kThreads, MINW) void ffn_down_bf16_kernel(FfnParams p) {
+  Group g;
+  if (!decode_item<kSharedFirst>(blockIdx.z, p.shared_items, p.max_work, p.n_work, p.work, p.row_token, p.T,
+                                 p.Tk, p.E, g))
+    return;
+  const int jt = blockIdx.x * RT;  // first of the RT packed tiles (H / 16 is a multiple of 8)
+  if (jt * 16 >= p.H) return;
+  __shared__ f32x4 red[3][RT][NT][kWave];
+  if constexpr (NT == 1) {
+    down_rows<true, NT, KMAX, BC, RT>(p, g, jt, 0, g.n, red);
+  } else {
+    const int pz = blockIdx.y * 16 * NT;
+    if (pz >= g.n) return;
+    if (g.n > 16 * NT)
+      down_rows<false, NT, KMAX, BC, RT>(p, g, jt, pz, min(g.n, pz + 16 * NT), red);
+    else
+      down_rows<true, NT, KMAX, BC, RT>(p, g, jt, 0, g.n, red);
   }
 }
 
@@ -708,7 +740,7 @@ template <int NT>
 hipError_t launch_bf16(const FfnParams& p, int ldh, int groups, hipStream_t s) {
   using S = Shape<NT>;
   const int passes = NT > 1 ? (std::min(p.T, DMOE_WORK_ROWS) + 16 * NT - 1) / (16 * NT) : 1;
-  const dim3 grid(ldh / (8 * S::kGuRows), groups, passes);
+  const dim3 grid(ldh / (8 * S::kGuRows), passes, groups);  // x: a multiple of 8
   // One pass of two token tiles over slices longer than the burst (one block
   // of 32 tokens, hidden 2048): the whole slice in one burst, issued before
   // the row list, 20.3 against 20.7 us for the FFN (two such blocks, two
@@ -725,7 +757,7 @@ hipError_t launch_bf16(const FfnParams& p, int ldh, int groups, hipStream_t s) {
         <<<grid, kThreads, 0, s>>>(p);
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
-  const dim3 grid_dn(p.H / (16 * S::kDnRows), groups, passes);
+  const dim3 grid_dn((p.H / (16 * S::kDnRows) + 7) / 8 * 8, passes, groups);
   if constexpr (NT == 1) {
     if (ldh / 128 > S::kDnMax) {
       ffn_down_bf16_kernel<NT, S::kDnLong, S::kDnChunk, S::kDnLongWaves, S::kSharedFirst, S::kDnRows>
