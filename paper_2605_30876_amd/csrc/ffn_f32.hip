@@ -50,6 +50,7 @@ struct F32Params {
   float* hbuf;      // SwiGLU activations [Tk (+ T)][ldh]
   float* slot_out;  // [T][k][H]
   float* shared_out;
+  int base;         // first unit (output feature) of the launch
 };
 
 // One burst of a wave's operands: NM weight matrices (gate and up, or down
@@ -96,7 +97,7 @@ __device__ __forceinline__ void mma_group(const float (&a)[4][NM][U], const f32x
 // used; a last group that K does not fill is loaded element by element, with
 // zeros past K in both operands.
 template <int U, int NM, int NT, bool kStream, bool kVecB>
-__device__ __forceinline__ void wave_dot_f32(const float* const (&W)[NM], uint32_t lo, size_t ldw, const float* const (&pb)[NT],
+__device__ __forceinline__ void wave_dot_f32(const float* const (&W)[NM], size_t lo, size_t ldw, const float* const (&pb)[NT],
                                              int bstep, int K, int g0, int g1, int q, f32x4 (&acc)[NM][U][NT]) {
   const int nfull = K / kGroup;
   const int ge = min(g1, nfull);
@@ -200,9 +201,9 @@ __device__ __forceinline__ void gateup_pass(const F32Params& p, const Group& g, 
   const int lane = threadIdx.x & 63, q = lane >> 4, c = lane & 15;
   const float* W = g.expert >= 0 ? p.w13 + static_cast<size_t>(g.expert) * 2 * p.I * p.H : p.ws13;
   const size_t ldw = 2 * static_cast<size_t>(Iw);
-  const int uc = min(u0 + U * c, Iw - U);  // units past the last: the last ones again, not stored
+  const int uc = u0 + min(U * c, Iw - U - u0);  // units past the last: the last ones again, not stored
   const float* const pw[2] = {W, W + Iw};
-  const uint32_t lo = 4 * q * static_cast<uint32_t>(ldw) + uc;
+  const size_t lo = 4 * q * ldw + uc;  // 64 bits: passes 2^32 from 179 million units on
   const float* pb[NT];
 #pragma unroll
   for (int ct = 0; ct < NT; ++ct) {
@@ -224,19 +225,19 @@ __device__ __forceinline__ void gateup_pass(const F32Params& p, const Group& g, 
       float* dst = p.hbuf + static_cast<size_t>(g.r0 + col) * p.ldh;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int u1 = u0 + U * (4 * q + r);
+        const int du = U * (4 * q + r);
         float h[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) h[u] = silu_f32(acc[0][u][ct][r]) * acc[1][u][ct][r];
-        if (u1 < Iw) {  // I % U == 0: the U units lie wholly in or past the row
+        if (du < Iw - u0) {  // I % U == 0: the U units lie wholly in or past the row
           if constexpr (U > 1) {
             typedef float vec __attribute__((ext_vector_type(U)));
             vec v;
 #pragma unroll
             for (int u = 0; u < U; ++u) v[u] = h[u];
-            *reinterpret_cast<vec*>(dst + u1) = v;
+            *reinterpret_cast<vec*>(dst + u0 + du) = v;
           } else {
-            dst[u1] = h[0];
+            dst[u0 + du] = h[0];
           }
         }
       }
@@ -252,7 +253,7 @@ __global__ __launch_bounds__(kThreads, 2) void ffn_gateup_f32_kernel(F32Params p
   Group g;
   if (!decode_item(blockIdx.y, 0, p.max_work, p.n_work, p.work, p.row_token, p.T, p.Tk, p.E, g)) return;
   const int Iw = g.expert >= 0 ? p.I : p.I_s;
-  const int u0 = blockIdx.x * 16 * U;
+  const int u0 = p.base + blockIdx.x * 16 * U;
   if (u0 >= Iw) return;
   const int p0 = blockIdx.z * kPassRows;
   if (p0 >= g.n) return;
@@ -268,9 +269,9 @@ __device__ __forceinline__ void down_pass(const F32Params& p, const Group& g, in
   const int lane = threadIdx.x & 63, q = lane >> 4, c = lane & 15;
   const int H = p.H;
   const float* W = g.expert >= 0 ? p.w2 + static_cast<size_t>(g.expert) * H * p.I : p.ws2;
-  const int jc = min(j0 + U * c, H - U);
+  const int jc = j0 + min(U * c, H - U - j0);
   const float* const pw[1] = {W};
-  const uint32_t lo = 4 * q * static_cast<uint32_t>(H) + jc;
+  const size_t lo = 4 * static_cast<size_t>(q) * H + jc;
   const float* pb[NT];
 #pragma unroll
   for (int ct = 0; ct < NT; ++ct)
@@ -290,13 +291,13 @@ __device__ __forceinline__ void down_pass(const F32Params& p, const Group& g, in
                          : p.shared_out + static_cast<size_t>(g.t0 + col) * H;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int j1 = j0 + U * (4 * q + r);
+        const int dj = U * (4 * q + r);
         if constexpr (U == 4) {
-          if (j1 < H)
-            *reinterpret_cast<f32x4*>(dst + j1) =
+          if (dj < H - j0)
+            *reinterpret_cast<f32x4*>(dst + j0 + dj) =
                 f32x4{acc[0][0][ct][r], acc[0][1][ct][r], acc[0][2][ct][r], acc[0][3][ct][r]};  // H % 4 == 0
         } else {
-          if (j1 < H) dst[j1] = acc[0][0][ct][r];
+          if (dj < H - j0) dst[j0 + dj] = acc[0][0][ct][r];
         }
       }
     }
@@ -311,7 +312,7 @@ __global__ __launch_bounds__(kThreads, 2) void ffn_down_f32_kernel(F32Params p) 
   Group g;
   if (!decode_item(blockIdx.y, 0, p.max_work, p.n_work, p.work, p.row_token, p.T, p.Tk, p.E, g)) return;
   const int Kd = g.expert >= 0 ? p.I : p.I_s;
-  const int j0 = blockIdx.x * 16 * U;
+  const int j0 = p.base + blockIdx.x * 16 * U;
   const int p0 = blockIdx.z * kPassRows;
   if (p0 >= g.n) return;
   if (g.n - p0 > 16)
@@ -326,7 +327,9 @@ __global__ __launch_bounds__(kThreads, 2) void ffn_down_f32_kernel(F32Params p) 
 // tiny layer of hidden 256, intermediate 128, 8 tokens: gate/up 4.8 us).
 constexpr int kWideGu = 2, kWideDn = 4;
 constexpr long kFillGroups = 256;
-
+// Workgroups in a grid's x dimension (a grid has fewer than 2^32 threads in
+// each): wider layers take several launches.
+constexpr int kMaxGridX = 1 << 23;
 
 }  // namespace
 
@@ -334,7 +337,7 @@ hipError_t launch_ffn_f32(const FfnArgs& a, int ldh, int items, hipStream_t s) {
   F32Params p{static_cast<const float*>(a.x), static_cast<const float*>(a.xr), static_cast<const float*>(a.w13), static_cast<const float*>(a.w2),
               static_cast<const float*>(a.ws13), static_cast<const float*>(a.ws2), a.sched.n_work, a.sched.work,
               a.sched.row_token, a.sched.row_slot, a.T, a.H, a.E, a.I, a.I_s, a.k, a.T * a.k, a.max_work, ldh,
-              static_cast<float*>(a.workspace), static_cast<float*>(a.slot_out), a.shared_out};
+              static_cast<float*>(a.workspace), static_cast<float*>(a.slot_out), a.shared_out, 0};
   // Items of few rows read their weights once per launch: non-temporal loads,
   // unless the selected experts' weights fit in half of the 256 MB
   // memory-side cache, where a layer called again finds them.  The layer at
@@ -344,41 +347,50 @@ hipError_t launch_ffn_f32(const FfnArgs& a, int ldh, int items, hipStream_t s) {
   const size_t weights = static_cast<size_t>(items) * 3 * a.H * ldh * sizeof(float);
   const bool stream = rows <= 32L * items && weights > (size_t{128} << 20);
   const bool wide_ok = a.I % kWideGu == 0 && a.I_s % kWideGu == 0;  // aligned loads and stores
-  const bool wide = wide_ok && static_cast<long>((ldh + 16 * kWideGu - 1) / (16 * kWideGu)) * items >= kFillGroups;
+  const bool wide = wide_ok && (static_cast<long>(ldh) + 16 * kWideGu - 1) / (16 * kWideGu) * items >= kFillGroups;
   // an item holds each token at most once
   const int passes = (std::min(a.T, DMOE_WORK_ROWS) + kPassRows - 1) / kPassRows;
   const int gu = wide ? 16 * kWideGu : 16;  // units per gate/up workgroup
-  const dim3 g_gu((ldh + gu - 1) / gu, items, passes);
-  if (wide) {
-    if (stream)
-      ffn_gateup_f32_kernel<kWideGu, true><<<g_gu, kThreads, 0, s>>>(p);
-    else
-      ffn_gateup_f32_kernel<kWideGu, false><<<g_gu, kThreads, 0, s>>>(p);
-  } else {
-    if (stream)
-      ffn_gateup_f32_kernel<1, true><<<g_gu, kThreads, 0, s>>>(p);
-    else
-      ffn_gateup_f32_kernel<1, false><<<g_gu, kThreads, 0, s>>>(p);
+  hipError_t err = hipSuccess;
+  const int gx_gu = static_cast<int>((static_cast<long>(ldh) + gu - 1) / gu);
+  for (int x = 0; x < gx_gu && err == hipSuccess; x += kMaxGridX) {
+    p.base = x * gu;
+    const dim3 grid(std::min(gx_gu - x, kMaxGridX), items, passes);
+    if (wide) {
+      if (stream)
+        ffn_gateup_f32_kernel<kWideGu, true><<<grid, kThreads, 0, s>>>(p);
+      else
+        ffn_gateup_f32_kernel<kWideGu, false><<<grid, kThreads, 0, s>>>(p);
+    } else {
+      if (stream)
+        ffn_gateup_f32_kernel<1, true><<<grid, kThreads, 0, s>>>(p);
+      else
+        ffn_gateup_f32_kernel<1, false><<<grid, kThreads, 0, s>>>(p);
+    }
+    err = hipGetLastError();
   }
-  hipError_t err = hipGetLastError();
-  if (err != hipSuccess) return err;
   const bool vec_b = ldh % 4 == 0;
-  const bool wide_dn = static_cast<long>((a.H + 16 * kWideDn - 1) / (16 * kWideDn)) * items >= kFillGroups;
+  const bool wide_dn = (static_cast<long>(a.H) + 16 * kWideDn - 1) / (16 * kWideDn) * items >= kFillGroups;
   const int du = wide_dn ? 16 * kWideDn : 16;
-  const dim3 g_dn((a.H + du - 1) / du, items, passes);
+  const int gx_dn = static_cast<int>((static_cast<long>(a.H) + du - 1) / du);
+  for (int x = 0; x < gx_dn && err == hipSuccess; x += kMaxGridX) {
+    p.base = x * du;
+    const dim3 grid(std::min(gx_dn - x, kMaxGridX), items, passes);
 #define DMOE_DOWN_F32(U_, S_, V_)                                 \
   if (wide_dn == (U_ == kWideDn) && stream == S_ && vec_b == V_) \
-    ffn_down_f32_kernel<U_, S_, V_><<<g_dn, kThreads, 0, s>>>(p);
-  DMOE_DOWN_F32(kWideDn, true, true)
-  DMOE_DOWN_F32(kWideDn, false, true)
-  DMOE_DOWN_F32(1, true, true)
-  DMOE_DOWN_F32(1, false, true)
-  DMOE_DOWN_F32(kWideDn, true, false)
-  DMOE_DOWN_F32(kWideDn, false, false)
-  DMOE_DOWN_F32(1, true, false)
-  DMOE_DOWN_F32(1, false, false)
+    ffn_down_f32_kernel<U_, S_, V_><<<grid, kThreads, 0, s>>>(p);
+    DMOE_DOWN_F32(kWideDn, true, true)
+    DMOE_DOWN_F32(kWideDn, false, true)
+    DMOE_DOWN_F32(1, true, true)
+    DMOE_DOWN_F32(1, false, true)
+    DMOE_DOWN_F32(kWideDn, true, false)
+    DMOE_DOWN_F32(kWideDn, false, false)
+    DMOE_DOWN_F32(1, true, false)
+    DMOE_DOWN_F32(1, false, false)
 #undef DMOE_DOWN_F32
-  return hipGetLastError();
+    err = hipGetLastError();
+  }
+  return err;
 }
 
 }  // namespace dmoe
