@@ -259,13 +259,20 @@ __global__ __launch_bounds__(256) void router_tile_bf16_kernel(
 // 16-expert tile per workgroup.  The eight waves split the hidden dimension in
 // groups of 16 features (lane (q, c) of a group holds features 4q .. 4q+3 of
 // its token and of its expert, one 16-byte load each), up to kF32Burst groups
-// in flight, and the partial tiles are summed in wave order.  What bounds it
+// in flight.  A wave keeps 16 partial tiles (four groups of a burst, four
+// instructions each) and all partial tiles are summed in pairs: chains of H /
+// 128 products, no longer than a sum spread over 64 lanes.  With one tile per
+// wave the chains were H / 8 long and the logits' distance from float64 grew:
+// hidden 256 1.2e-7 of the logits (7.8e-8 now; 64 lanes 7.8e-8), 1024 2.1e-7
+// (9.0e-8; 1.0e-7), 2048 2.9e-7 (1.0e-7; 1.2e-7), at the same time.  What bounds it
 // is one memory round trip: a wave per (token, 4 experts) with a 64-lane
 // reduction per dot product, which it replaces, took 25 us for 64 tokens x 32
 // experts at hidden 1024.  kVec: rows are 16-byte aligned (H % 4 == 0); a
 // last group past H is masked in both operands.
 constexpr int kF32RouterWaves = 8;
 constexpr int kF32Burst = 8;
+constexpr int kF32Chains = 4;  // times the four instructions of a group: 16 sums per wave
+static_assert(kF32RouterWaves == 8 && kF32Burst % kF32Chains == 0, "sums in pairs");
 
 template <bool kVec>
 __global__ __launch_bounds__(kF32RouterWaves * kWave) void router_logits_f32_kernel(
@@ -280,7 +287,11 @@ __global__ __launch_bounds__(kF32RouterWaves * kWave) void router_logits_f32_ker
   const int ng = (H + 15) / 16, per = (ng + kF32RouterWaves - 1) / kF32RouterWaves;
   const int g0 = wave * per, g1 = min(ng, g0 + per);
   const bool write_x = xk && blockIdx.y == 0 && t0 + c < T;  // x_chunked needs H % 4 == 0
-  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  f32x4 acc[kF32Chains][4];
+#pragma unroll
+  for (int j = 0; j < kF32Chains; ++j)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
   for (int gb = g0; gb < g1; gb += kF32Burst) {
     f32x4 a[kF32Burst], b[kF32Burst];
 #pragma unroll
@@ -307,22 +318,32 @@ __global__ __launch_bounds__(kF32RouterWaves * kWave) void router_logits_f32_ker
       const bool in = !kVec || 16 * g + 4 * q < H;
 #pragma unroll
       for (int i = 0; i < 4; ++i)
-        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(in ? a[s][i] : 0.f, in ? b[s][i] : 0.f, acc, 0, 0, 0);
+        acc[s % kF32Chains][i] =
+            __builtin_amdgcn_mfma_f32_16x16x4f32(in ? a[s][i] : 0.f, in ? b[s][i] : 0.f, acc[s % kF32Chains][i], 0, 0, 0);
       if (kVec && write_x && in)
         *reinterpret_cast<f32x4*>(xk + (static_cast<size_t>(4 * g + q) * T + t0 + c) * 4) = a[s];
     }
   }
-  if (wave > 0) red[wave - 1][lane] = acc;
+#pragma unroll
+  for (int n = kF32Chains / 2; n > 0; n /= 2)
+#pragma unroll
+    for (int j = 0; j < n; ++j)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc[j][i] += acc[j + n][i];
+  const f32x4 part_sum = (acc[0][0] + acc[0][1]) + (acc[0][2] + acc[0][3]);
+  if (wave > 0) red[wave - 1][lane] = part_sum;
   __syncthreads();
   if (wave != 0) return;
-#pragma unroll
-  for (int ww = 0; ww < kF32RouterWaves - 1; ++ww) acc += red[ww][lane];
+  // the eight waves in pairs, then fours
+  const f32x4 lo = (part_sum + red[0][lane]) + (red[1][lane] + red[2][lane]);
+  const f32x4 hi = (red[3][lane] + red[4][lane]) + (red[5][lane] + red[6][lane]);
+  const f32x4 sum = lo + hi;
   const int e = e0 + c;
   if (e >= E) return;
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     const int t = t0 + 4 * q + r;
-    if (t < T) part[static_cast<size_t>(t) * E + e] = acc[r];
+    if (t < T) part[static_cast<size_t>(t) * E + e] = sum[r];
   }
 }
 
