@@ -25,6 +25,7 @@
 // U = 2, 80 with the passes spread over workgroups.  fp32 rounding only: the
 // distance from float64 is that of the scalar kernels (4.8e-7 of the output).
 #include <algorithm>
+#include <type_traits>
 
 #include "dmoe_common.h"
 #include "ffn_dev.h"
@@ -245,6 +246,30 @@ __device__ __forceinline__ void gateup_pass(const F32Params& p, const Group& g, 
   }
 }
 
+// f(token tiles of the pass, non-temporal weight loads).  An item of several
+// passes is read by as many workgroups, whose later ones can find its weights
+// in a cache: plain loads, also in a launch that streams.  Token routing,
+// us per layer, layers in rotation: two blocks of 32 tokens over 128 experts
+// (hidden 768, intermediate 384) 110.0 -> 108.4, Zipf-biased 70.0 -> 67.2,
+// four of 48 93.6 -> 88.1.  (The passes of an item adjacent in the grid, as in
+// the bf16 kernels, measured 110 -> 195: rows that hold no work between the
+// others.)
+template <bool kStream, typename F>
+__device__ __forceinline__ void by_rows(const Group& g, int p0, F f) {
+  constexpr std::integral_constant<int, 1> one;
+  constexpr std::integral_constant<int, 2> two;
+  if (kStream && g.n <= kPassRows) {
+    if (g.n > 16)
+      f(two, std::bool_constant<kStream>{});
+    else
+      f(one, std::bool_constant<kStream>{});
+  } else if (g.n - p0 > 16) {
+    f(two, std::false_type{});
+  } else {
+    f(one, std::false_type{});
+  }
+}
+
 // grid (ceil(ldh / (16 U)), items, passes): units 16*U*bx .. of rows 32*bz ..
 // of item y.  I % U == 0 and I_s % U == 0 (aligned loads and stores).
 template <int U, bool kStream>
@@ -257,10 +282,9 @@ __global__ __launch_bounds__(kThreads, 2) void ffn_gateup_f32_kernel(F32Params p
   if (u0 >= Iw) return;
   const int p0 = blockIdx.z * kPassRows;
   if (p0 >= g.n) return;
-  if (g.n - p0 > 16)
-    gateup_pass<U, 2, kStream>(p, g, Iw, u0, p0, red);
-  else
-    gateup_pass<U, 1, kStream>(p, g, Iw, u0, p0, red);
+  by_rows<kStream>(g, p0, [&](auto nt, auto stream) {
+    gateup_pass<U, decltype(nt)::value, decltype(stream)::value>(p, g, Iw, u0, p0, red);
+  });
 }
 
 template <int U, int NT, bool kStream, bool kVecB>
@@ -315,10 +339,9 @@ __global__ __launch_bounds__(kThreads, 2) void ffn_down_f32_kernel(F32Params p) 
   const int j0 = p.base + blockIdx.x * 16 * U;
   const int p0 = blockIdx.z * kPassRows;
   if (p0 >= g.n) return;
-  if (g.n - p0 > 16)
-    down_pass<U, 2, kStream, kVecB>(p, g, Kd, j0, p0, red);
-  else
-    down_pass<U, 1, kStream, kVecB>(p, g, Kd, j0, p0, red);
+  by_rows<kStream>(g, p0, [&](auto nt, auto stream) {
+    down_pass<U, decltype(nt)::value, decltype(stream)::value, kVecB>(p, g, Kd, j0, p0, red);
+  });
 }
 
 // Units per lane: gate/up 2 (two matrices; at 4 the operands leave one burst
@@ -338,11 +361,15 @@ hipError_t launch_ffn_f32(const FfnArgs& a, int ldh, int items, hipStream_t s) {
               static_cast<const float*>(a.ws13), static_cast<const float*>(a.ws2), a.sched.n_work, a.sched.work,
               a.sched.row_token, a.sched.row_slot, a.T, a.H, a.E, a.I, a.I_s, a.k, a.T * a.k, a.max_work, ldh,
               static_cast<float*>(a.workspace), static_cast<float*>(a.slot_out), a.shared_out, 0};
-  // Items of few rows read their weights once per launch: non-temporal loads,
-  // unless the selected experts' weights fit in half of the 256 MB
-  // memory-side cache, where a layer called again finds them.  The layer at
-  // the top of the file, token routing (207 MB) 78.9 us against 82.6 with plain loads; block
-  // routing (57 MB) 68.0 against 54.1.
+  // Items of few rows read their weights once per launch: non-temporal loads
+  // (by_rows), where the weights of all items, an upper bound of what is read,
+  // exceed 128 MiB.  Layers in rotation, so that weights come from HBM, us per
+  // layer, plain / non-temporal loads throughout: the layer at the top of
+  // the file, token routing (207 MB at most) 85.4 / 81.5, one block of 8 tokens 70.4 / 66.7;
+  // smaller launches mostly the other way: block routing (57 MB) 65.6 / 73.4,
+  // one block of 8 (31 MB) 34.6 / 37.1, a layer of hidden 768 and intermediate 384 50.0
+  // / 59.3, of hidden 256 20.4 / 21.4; but token routing over many experts
+  // (117 MB at most) 49.0 / 46.0, and 30.8 / 32.5 when few are popular.
   const long rows = static_cast<long>(a.T) * std::max(a.k, 1);
   const size_t weights = static_cast<size_t>(items) * 3 * a.H * ldh * sizeof(float);
   const bool stream = rows <= 32L * items && weights > (size_t{128} << 20);

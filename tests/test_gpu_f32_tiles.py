@@ -22,6 +22,18 @@ SHAPES = {
     "wide_ragged": dict(H=260, E=24, I=604, I_s=596, k=4, NB=2, bs=33),
     "many_rows": dict(H=68, E=4, I=64, I_s=40, k=2, NB=5, bs=64),
     "wide_pieces": dict(H=512, E=40, I=448, I_s=448, k=2, NB=9, bs=40),
+    # wide down workgroups over activation rows that are not 16-byte aligned
+    "wide_down_odd": dict(H=2048, E=8, I=37, I_s=0, k=2, NB=4, bs=8),
+}
+
+# Token routing over more than 128 MiB of weights (non-temporal loads): narrow
+# and wide workgroups of both kernels, aligned and unaligned activation rows,
+# items of one pass and (popular experts, the shared expert) of several.
+STREAM = {
+    "odd_units": dict(H=2048, E=48, I=201, I_s=201, k=4, NB=4, bs=20),
+    "narrow": dict(H=128, E=64, I=1400, I_s=1400, k=4, NB=1, bs=16),
+    "narrow_odd": dict(H=128, E=64, I=1401, I_s=1401, k=4, NB=1, bs=16),
+    "passes": dict(H=512, E=48, I=604, I_s=604, k=4, NB=4, bs=20),
 }
 
 
@@ -33,6 +45,18 @@ def test_f32_layer_edges(gpu_lib, name, routing):
     d = {k: (None if v is None else v.cuda()) for k, v in make_inputs(cfg, seed=5).items()}
     m = MoELayer(cfg.H, cfg.E, cfg.I, cfg.I_s, cfg.k, cfg.NB, cfg.bs, dtype=torch.float32, device="cuda")
     run_and_check(cfg, d, routing, m)
+
+
+@pytest.mark.parametrize("name", list(STREAM))
+def test_f32_layer_streaming(gpu_lib, name):
+    cfg = get_config("small_f32").with_(name="f32_stream_" + name, bias="zipf", **STREAM[name])
+    print("case", name, flush=True)
+    d = {k: (None if v is None else v.cuda()) for k, v in make_inputs(cfg, seed=11).items()}
+    m = MoELayer(cfg.H, cfg.E, cfg.I, cfg.I_s, cfg.k, cfg.NB, cfg.bs, dtype=torch.float32, device="cuda")
+    assert (m.max_work("token") + 1) * 3 * cfg.H * max(cfg.I, cfg.I_s) * 4 > 128 << 20
+    run_and_check(cfg, d, "token", m)
+    if cfg.T > 32:
+        assert int(m.sched.work[:int(m.sched.n_work[0]), 2].max()) > 32  # an item of several passes
 
 
 @pytest.mark.parametrize("T,H,E", [(1, 1, 1), (16, 16, 16), (17, 33, 19), (5, 130, 300), (40, 1024, 33)])
