@@ -88,6 +88,7 @@ struct FfnParams {
   void* slot_out;                          // [T][k][H], float32 or scaled half (slot_f16s)
   float* shared_out;
   int slot_f16s;
+  int adjacent;  // passes of an item: grid dimension y, the items z (else the other way round)
 };
 
 // Four consecutive outputs j0 .. j0+3 of schedule row r (token row_token[r],
@@ -182,35 +183,32 @@ __device__ __forceinline__ void gateup_rows(const FfnParams& p, const Group& g, 
   }
 }
 
-// One token tile: a workgroup takes all 16-row passes of its item, over
-// weights held in registers.  More: one pass of 16*NT rows per workgroup
-// (these launches are small, and the passes of an item of many rows, the
-// shared expert's above all, were their long pole: five blocks of 24 tokens
-// over 48 experts 50.6 -> 47.8 us per layer).  Grid (tiles, passes, items): an
-// item's passes are dispatched one after the other, tiles a multiple of 8, so
-// that the passes of one tile meet on one XCD, and load their weights
-// plainly: the later ones find them in that XCD's L2.  Hidden 2048, 128
-// experts of intermediate 512, top-8, Zipf-biased router, us per layer, one
-// workgroup running all passes over held weights / passes in the slowest grid
-// dimension, non-temporal / these: three blocks of 32 tokens 59.4 / 68.6 /
-// 54.8, six of 24 74.0 / 89.0 / 71.4; unbiased 71.8 / 69.5 / 64.7 and 99.5 /
-// 99.5 / 90.3.  (Both load types in one body spilled: 128 B a lane, 61.8 us
-// for two blocks of 32 against 52.6.)
+// A workgroup takes all passes of its item, over weights that one burst keeps
+// in registers, or (kSplit: two and four token tiles) one pass of 16*NT rows:
+// these launches are small, and the passes of an item of many rows, the
+// shared expert's above all, were their long pole (five blocks of 24 tokens
+// over 48 experts 50.6 -> 47.8 us per layer).  The passes' workgroups load an
+// item's weights plainly when there are several, so that the later ones find
+// them in a cache.  They come one grid layer after the other, or (adjacent)
+// one after the other for each item, tiles a multiple of 8, so that the
+// passes of a tile meet in one XCD's L2: launch_decode's callers choose.
+// (Both load types in one body spilled: 128 B a lane, two blocks of 32 tokens
+// 61.8 us against 52.6.)
 // Packed gate/up tile `it` = 8 intermediate units.
-template <int NT, int KMAX, int BC, int MINW, bool kSharedFirst, int RT>
+template <int NT, int KMAX, int BC, int MINW, bool kSharedFirst, int RT, bool kSplit>
 __global__ __launch_bounds__(kThreads, MINW) void ffn_gateup_bf16_kernel(FfnParams p) {
   Group g;
-  if (!decode_item<kSharedFirst>(blockIdx.z, p.shared_items, p.max_work, p.n_work, p.work, p.row_token, p.T,
+  if (!decode_item<kSharedFirst>(kSplit && p.adjacent ? blockIdx.z : blockIdx.y, p.shared_items, p.max_work, p.n_work, p.work, p.row_token, p.T,
                                  p.Tk, p.E, g))
     return;
   const int Iw = g.expert >= 0 ? p.I : p.I_s;
   const int it = blockIdx.x * RT;  // first of the RT packed tiles (Iw / 8 is a multiple of 16)
   if (it * 8 >= Iw) return;
   __shared__ f32x4 red[3][RT][NT][kWave];
-  if constexpr (NT == 1) {
+  if constexpr (!kSplit) {
     gateup_rows<true, NT, KMAX, BC, RT>(p, g, it, 0, g.n, red);
   } else {
-    const int pz = blockIdx.y * 16 * NT;
+    const int pz = (p.adjacent ? blockIdx.y : blockIdx.z) * 16 * NT;
     if (pz >= g.n) return;
     if (g.n > 16 * NT)
       gateup_rows<false, NT, KMAX, BC, RT>(p, g, it, pz, min(g.n, pz + 16 * NT), red);
@@ -270,19 +268,19 @@ __device__ __forceinline__ void down_rows(const FfnParams& p, const Group& g, in
   }
 }
 
-template <int NT, int KMAX, int BC, int MINW, bool kSharedFirst, int RT>
+template <int NT, int KMAX, int BC, int MINW, bool kSharedFirst, int RT, bool kSplit>
 __global__ __launch_bounds__(kThreads, MINW) void ffn_down_bf16_kernel(FfnParams p) {
   Group g;
-  if (!decode_item<kSharedFirst>(blockIdx.z, p.shared_items, p.max_work, p.n_work, p.work, p.row_token, p.T,
+  if (!decode_item<kSharedFirst>(kSplit && p.adjacent ? blockIdx.z : blockIdx.y, p.shared_items, p.max_work, p.n_work, p.work, p.row_token, p.T,
                                  p.Tk, p.E, g))
     return;
   const int jt = blockIdx.x * RT;  // first of the RT packed tiles (H / 16 is a multiple of 8)
   if (jt * 16 >= p.H) return;
   __shared__ f32x4 red[3][RT][NT][kWave];
-  if constexpr (NT == 1) {
+  if constexpr (!kSplit) {
     down_rows<true, NT, KMAX, BC, RT>(p, g, jt, 0, g.n, red);
   } else {
-    const int pz = blockIdx.y * 16 * NT;
+    const int pz = (p.adjacent ? blockIdx.y : blockIdx.z) * 16 * NT;
     if (pz >= g.n) return;
     if (g.n > 16 * NT)
       down_rows<false, NT, KMAX, BC, RT>(p, g, jt, pz, min(g.n, pz + 16 * NT), red);
@@ -726,6 +724,7 @@ struct Shape<1> {
 template <>
 struct Shape<2> {
   static constexpr int kGuMax = 8, kGuChunk = 4, kGuWaves = 4, kDnMax = 4, kDnChunk = 4, kDnWaves = 3;
+  static constexpr int kGuLong = 16, kGuLongWaves = 3;  // a slice held across passes, or of one pass
   static constexpr int kGuRows = 1, kDnRows = 2;
   static constexpr bool kSharedFirst = false;
 };
@@ -736,38 +735,78 @@ struct Shape<4> {
   static constexpr bool kSharedFirst = false;
 };
 
-template <int NT>
-hipError_t launch_bf16(const FfnParams& p, int ldh, int groups, hipStream_t s) {
+// kSplit: a pass per workgroup.
+template <int NT, bool kSplit, int kGuMax = Shape<NT>::kGuMax, int kGuWaves = Shape<NT>::kGuWaves,
+          int kDnMax = Shape<NT>::kDnMax, int kDnWaves = Shape<NT>::kDnWaves>
+hipError_t launch_decode(const FfnParams& p, int ldh, int groups, int passes, hipStream_t s) {
   using S = Shape<NT>;
-  const int passes = NT > 1 ? (std::min(p.T, DMOE_WORK_ROWS) + 16 * NT - 1) / (16 * NT) : 1;
-  const dim3 grid(ldh / (8 * S::kGuRows), passes, groups);  // x: a multiple of 8
-  // One pass of two token tiles over slices longer than the burst (one block
-  // of 32 tokens, hidden 2048): the whole slice in one burst, issued before
-  // the row list, 20.3 against 20.7 us for the FFN (two such blocks, two
-  // passes: 56.5 against 55.5 per layer).
-  bool launched = false;
-  if constexpr (NT == 2) {
-    if (passes == 1 && p.H / 128 > S::kGuMax) {
-      ffn_gateup_bf16_kernel<NT, 16, 4, 3, S::kSharedFirst, S::kGuRows><<<grid, kThreads, 0, s>>>(p);
-      launched = true;
-    }
-  }
-  if (!launched)
-    ffn_gateup_bf16_kernel<NT, S::kGuMax, S::kGuChunk, S::kGuWaves, S::kSharedFirst, S::kGuRows>
-        <<<grid, kThreads, 0, s>>>(p);
-  hipError_t err = hipGetLastError();
+  // tiles: a multiple of 8 (see the kernels), the down projection's rounded up
+  const int gx_gu = ldh / (8 * S::kGuRows), gx_dn = (p.H / (16 * S::kDnRows) + 7) / 8 * 8;
+  const int gy = p.adjacent ? passes : groups, gz = p.adjacent ? groups : passes;
+  ffn_gateup_bf16_kernel<NT, kGuMax, S::kGuChunk, kGuWaves, S::kSharedFirst, S::kGuRows, kSplit>
+      <<<dim3(gx_gu, gy, gz), kThreads, 0, s>>>(p);
+  const hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
-  const dim3 grid_dn((p.H / (16 * S::kDnRows) + 7) / 8 * 8, passes, groups);
-  if constexpr (NT == 1) {
-    if (ldh / 128 > S::kDnMax) {
-      ffn_down_bf16_kernel<NT, S::kDnLong, S::kDnChunk, S::kDnLongWaves, S::kSharedFirst, S::kDnRows>
-          <<<grid_dn, kThreads, 0, s>>>(p);
-      return hipGetLastError();
-    }
-  }
-  ffn_down_bf16_kernel<NT, S::kDnMax, S::kDnChunk, S::kDnWaves, S::kSharedFirst, S::kDnRows>
-      <<<grid_dn, kThreads, 0, s>>>(p);
+  ffn_down_bf16_kernel<NT, kDnMax, S::kDnChunk, kDnWaves, S::kSharedFirst, S::kDnRows, kSplit>
+      <<<dim3(gx_dn, gy, gz), kThreads, 0, s>>>(p);
   return hipGetLastError();
+}
+
+hipError_t launch_one_tile(const FfnParams& p, int ldh, int items, hipStream_t s) {
+  using S = Shape<1>;
+  if (ldh / 128 > S::kDnMax)
+    return launch_decode<1, false, S::kGuMax, S::kGuWaves, S::kDnLong, S::kDnLongWaves>(p, ldh, items, 1, s);
+  return launch_decode<1, false>(p, ldh, items, 1, s);
+}
+
+// Two token tiles.  How the passes of an item run, us per layer, one
+// workgroup for all / a grid layer per pass / adjacent:
+//  * Adjacent where the weights stream long enough (hidden 1024 and up: slices
+//    of a whole burst and more) for the later passes to miss the caches, and
+//    some item is sure to have several (the shared expert) or the launch is
+//    large: nine blocks of 32 under Top-P, hidden 3840, intermediate 1408, 521 /
+//    540 / 462; six of 24 with a shared expert, hidden 4096, intermediate 1536,
+//    432 / 383 / 346, hidden 1024, intermediate 1024, Zipf-biased, 91 / 80 / 72;
+//    three of 32, hidden 2048, intermediate 512, Zipf-biased, 58.5 / 57.0 / 55.0.
+//    Not with few tiles: dispatch is round-robin over the CUs, and the passes
+//    without rows, a few workgroups each between those that have some, leave
+//    CUs without work (intermediate 384, 48 tiles, 36 blocks of 16 tokens over
+//    148 experts 367 / 354 / 377; intermediate 256, two of 32 52.0 / 51.8 / 57.2;
+//    intermediate 128, ten of 10 43.2 / 43.3 / 47.7).
+//  * One workgroup for all in launches of many items, most of whose passes
+//    would have no rows, where holding the weights saves reads: slices that are
+//    one burst at its length but two at the others' (hidden 1280, intermediate
+//    384, 14 blocks of 40 under Top-P, 162 items 135 / 149 / 137; hidden 1536, 19
+//    of 32, 194 items 112 / 122 / 124), and in large launches those of more than
+//    half a short burst (hidden 1024, intermediate 384, 12 of 61, token routing,
+//    308 items 133 / 144 / 149; hidden 768, 11 of 64 under Top-P, 267 items 156 /
+//    160 / 165; at hidden 384, 34 of 32, 271 items, 374 / 353 / 366).
+//  * A grid layer per pass otherwise (five blocks of 24 over 48, hidden 768,
+//    intermediate 384: 45.5 / 38.8 / 39.1).
+constexpr int kAdjacentHidden = 1024, kAdjacentTiles = 64;
+constexpr long kLargeLaunch = 8192;  // gate/up workgroups of one pass
+constexpr int kManyItems = 128;
+
+hipError_t launch_two_tiles(FfnParams p, int ldh, int items, hipStream_t s) {
+  using S = Shape<2>;
+  const int passes = (std::min(p.T, DMOE_WORK_ROWS) + 31) / 32;
+  const int gx = ldh / 8, steps = p.H / 128;
+  // One pass over slices longer than the burst (one block of 32 tokens, hidden
+  // 2048): the whole slice in one burst, issued before the row list, 20.3
+  // against 20.7 us for the FFN (two such blocks, two passes: 56.5 against
+  // 55.5 per layer).
+  if (passes == 1 && steps > S::kGuMax)
+    return launch_decode<2, true, S::kGuLong, S::kGuLongWaves>(p, ldh, items, 1, s);
+  const bool large = static_cast<long>(gx) * items >= kLargeLaunch;
+  p.adjacent = p.H >= kAdjacentHidden && gx >= kAdjacentTiles && (large || p.shared_items > 0);
+  const bool hold = steps > S::kGuMax ? steps <= S::kGuLong : large && steps > S::kGuMax / 2;
+  if (passes > 1 && !p.adjacent && items >= kManyItems && hold)
+    return launch_decode<2, false, S::kGuLong, S::kGuLongWaves>(p, ldh, items, 1, s);
+  return launch_decode<2, true>(p, ldh, items, passes, s);
+}
+
+hipError_t launch_four_tiles(const FfnParams& p, int ldh, int items, hipStream_t s) {
+  return launch_decode<4, true>(p, ldh, items, (std::min(p.T, DMOE_WORK_ROWS) + 63) / 64, s);
 }
 
 // Tile kernels, one item per workgroup.  Two weight tiles per wave halve the
@@ -843,7 +882,7 @@ hipError_t launch_ffn(const FfnArgs& a, dmoe_dtype dt, hipStream_t s) {
                 static_cast<const bf16_t*>(a.ws2), a.sched.n_work, a.sched.work, a.sched.row_token,
                 a.sched.row_slot, a.T, a.H, a.E, a.I, a.I_s, a.k, Tk, R, a.max_work, shared_items,
                 static_cast<bf16_t*>(a.workspace), a.slot_out, a.shared_out,
-                a.slot_fmt == DMOE_SLOT_F16S ? 1 : 0};
+                a.slot_fmt == DMOE_SLOT_F16S ? 1 : 0, 0};
     if (use_tile_kernels(a.T, a.k, a.max_work, items, ldh)) {
       return launch_tiles(p, ldh, items, rows_per_item(a.T, a.k, a.max_work), s);
     }
@@ -867,10 +906,10 @@ hipError_t launch_ffn(const FfnArgs& a, dmoe_dtype dt, hipStream_t s) {
         if (a.T > kPassRows && (multi_burst || pass_per_expert)) {
           return launch_tiles(p, ldh, items, rows_per_item(a.T, a.k, a.max_work), s);
         }
-        return launch_bf16<1>(p, ldh, items, s);
+        return launch_one_tile(p, ldh, items, s);
       }
-      case 2: return launch_bf16<2>(p, ldh, items, s);
-      default: return launch_bf16<4>(p, ldh, items, s);
+      case 2: return launch_two_tiles(p, ldh, items, s);
+      default: return launch_four_tiles(p, ldh, items, s);
     }
   }
   return launch_ffn_f32(a, ldh, items, s);
