@@ -271,11 +271,11 @@ __global__ __launch_bounds__(256) void router_tile_bf16_kernel(
 // last group past H is masked in both operands.
 constexpr int kF32RouterWaves = 8;
 constexpr int kF32Burst = 8;
-constexpr int kF32Chains = 4;  // times the four instructions of a group: 16 sums per wave
+constexpr int kF32Chains = 2;  // times the four instructions of a group: 16 sums per wave
 static_assert(kF32RouterWaves == 8 && kF32Burst % kF32Chains == 0, "sums in pairs");
 
 template <bool kVec>
-__global__ __launch_bounds__(kF32RouterWaves * kWave) void router_logits_f32_kernel(
+__global__ __launch_bounds__(kF32RouterWaves * kWave, 4) void router_logits_f32_kernel(
     const float* __restrict__ x, const float* __restrict__ w, int T, int H, int E,
     float* __restrict__ part, float* __restrict__ xk) {
   __shared__ f32x4 red[kF32RouterWaves - 1][kWave];
