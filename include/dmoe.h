@@ -264,9 +264,9 @@ dmoe_status dmoe_build_expert_schedule(const int32_t* experts, int n_groups, int
  *   dmoe_block_aggregate_topk(probs, n_blocks, block_size, E, k, ...)
  *   dmoe_build_expert_schedule(block_experts, n_blocks, block_size, k, E, sched)
  * with T = n_blocks*block_size, arguments as documented there, and results
- * bit-identical to that sequence.  When a block's probabilities fit in on-chip
- * memory, a forward of one block runs as two kernels and one of several
- * blocks as three, instead of four.
+ * bit-identical to that sequence.  Where it is faster (blocks of up to 16 to 64
+ * tokens, by their number and E), a forward of one block runs as two kernels
+ * and one of several blocks as three, instead of four.
  * Limits: the union of the three calls' limits (E <= 512).
  */
 dmoe_status dmoe_route_block(const void* x, const void* w_router, const float* bias, dmoe_dtype dt,

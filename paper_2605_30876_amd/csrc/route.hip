@@ -5,9 +5,9 @@
 //
 // A decode step routes few tokens; its routing kernels are bound by memory
 // round trips (each kernel boundary adds a write, a cache flush and a re-read
-// from another XCD), not by arithmetic.  When a block's logits fit in
-// LDS, everything after the router runs in one workgroup per block with a
-// single round trip: all partial logits are loaded at once, then softmax
+// from another XCD), not by arithmetic.  Blocks of up to 16 to 64 tokens
+// (route_block_fits) run everything after the router in one workgroup each
+// with a single round trip: all partial logits are loaded at once, then softmax
 // rows (into LDS), block sums, top-k and combine weights run on chip, and for
 // a forward of one block the schedule too.  (Token routing has T rows to select; spread
 // over T/4 workgroups it is faster, so it runs the softmax and each token's
@@ -24,9 +24,9 @@ namespace {
 
 constexpr int kThreads = dev::kSchedThreads;  // the schedule's workgroup size
 constexpr int kWaves = kThreads / kWave;
-// Two workgroups per CU, with headroom for static LDS.  Blocks of 64 tokens
-// over 256 experts (68 KB) fit: 64 such blocks 428.2 -> 425.5 us per layer
-// against separate softmax and block top-k launches, 16 197.0 -> 195.3.
+// The largest block that gains (64 tokens over 256 experts: 68 KB), with
+// headroom for static LDS.  (The registers leave one workgroup per CU either
+// way.)
 constexpr size_t kMaxLdsBytes = 76 * 1024;
 
 // LDS words of the block kernel (4-byte words; rows padded to a multiple of 4
@@ -168,10 +168,25 @@ __global__ __launch_bounds__(kThreads) void route_small_kernel(
 
 }  // namespace
 
-// One workgroup per block when a block's rows fit in LDS.
-static bool route_block_fits(int gs, int E, int k) {
+// One workgroup per block when a block's rows fit in LDS and it is faster than
+// separate softmax and block top-k launches, which spread the rows over the
+// chip: its eight waves take the rows four at a time, so it pays by the row,
+// and more for rows that are not 16-byte aligned (scalar loads).  Routing of
+// blocks over E experts (hidden 512 to 2048, top-8), us, one workgroup /
+// separate:
+//   aligned, E = 256: 2 x 32 15.9 / 18.2, 2 x 64 19.0 / 19.9, 64 x 64 25.7 / 30.6,
+//     2 x 96 22.6 / 22.0; E = 192: 2 x 48 19.5 / 19.5, 24 x 64 26.0 / 27.2; E = 128:
+//     2 x 32 17.3 / 17.9, 2 x 48 19.9 / 19.0, 8 x 128 31.3 / 25.2
+//   not aligned, E = 219: 8 x 16 17.8 / 18.7, 8 x 24 20.8 / 19.7, 8 x 64 31.1 / 21.9
+//   one block, where separate launches also schedule in one of their own:
+//     E = 128: 48 17.1 / 18.6, 64 18.5 / 18.9, 96 23.1 / 21.1; not aligned, E = 101:
+//     32 15.8 / 17.1, 64 21.5 / 19.0; E = 219: 32 19.1 / 18.6; E = 301: 16 17.7 /
+//     20.9, 32 24.5 / 21.8
+static bool route_block_fits(int G, int gs, int E, int k) {
   if (E > dev::kRegSoftmaxMaxE || k > dev::kMaxK) return false;
-  return fused_layout(gs, E, k).total * sizeof(float) <= kMaxLdsBytes;
+  if (fused_layout(gs, E, k).total * sizeof(float) > kMaxLdsBytes) return false;
+  if (E % 4) return gs * (E > 256 ? 2 : 1) <= (G == 1 ? 32 : 16);
+  return gs <= (G == 1 || E >= 192 ? 64 : 32);
 }
 
 // Alg. 1 with the Top-P coreset: the router, every token's own top-k (with
@@ -204,7 +219,7 @@ static hipError_t launch_route_topp(const RouteArgs& a, dmoe_dtype dt, hipStream
 hipError_t launch_route(const RouteArgs& a, dmoe_dtype dt, hipStream_t s) {
   if (a.topp) return launch_route_topp(a, dt, s);
   const int G = a.block ? a.T / a.gs : a.T;
-  if (a.block && route_block_fits(a.gs, a.E, a.k)) {
+  if (a.block && route_block_fits(G, a.gs, a.E, a.k)) {
     float* part = nullptr;
     int S = 1;
     hipError_t err = launch_router_partials(a.x, a.w, dt, a.T, a.H, a.E, a.probs, a.x_chunked, a.workspace,

@@ -259,19 +259,20 @@ __global__ __launch_bounds__(256) void router_tile_bf16_kernel(
 // 16-expert tile per workgroup.  The eight waves split the hidden dimension in
 // groups of 16 features (lane (q, c) of a group holds features 4q .. 4q+3 of
 // its token and of its expert, one 16-byte load each), up to kF32Burst groups
-// in flight.  A wave keeps 16 partial tiles (four groups of a burst, four
-// instructions each) and all partial tiles are summed in pairs: chains of H /
-// 128 products, no longer than a sum spread over 64 lanes.  With one tile per
-// wave the chains were H / 8 long and the logits' distance from float64 grew:
-// hidden 256 1.2e-7 of the logits (7.8e-8 now; 64 lanes 7.8e-8), 1024 2.1e-7
-// (9.0e-8; 1.0e-7), 2048 2.9e-7 (1.0e-7; 1.2e-7), at the same time.  What bounds it
+// in flight.  A wave keeps eight partial tiles (two groups of a burst, four
+// instructions each) and all partial tiles are summed in pairs: as many
+// partial sums as 64 lanes make, and the same distance from float64 (hidden
+// 256 7.8e-8 of the logits, 1024 1.0e-7, 2048 1.2e-7).  With one tile per wave
+// it was 1.2e-7, 2.1e-7 and 2.9e-7; with 16 7.8e-8, 9.0e-8 and 1.0e-7, but 158
+// registers and so one workgroup per CU (58.6 -> 61.0 us per layer for 31
+// blocks of 64 tokens over 208 experts; 59.0 with eight).  What bounds it
 // is one memory round trip: a wave per (token, 4 experts) with a 64-lane
 // reduction per dot product, which it replaces, took 25 us for 64 tokens x 32
 // experts at hidden 1024.  kVec: rows are 16-byte aligned (H % 4 == 0); a
 // last group past H is masked in both operands.
 constexpr int kF32RouterWaves = 8;
 constexpr int kF32Burst = 8;
-constexpr int kF32Chains = 2;  // times the four instructions of a group: 16 sums per wave
+constexpr int kF32Chains = 2;  // times the four instructions of a group: eight sums per wave
 static_assert(kF32RouterWaves == 8 && kF32Burst % kF32Chains == 0, "sums in pairs");
 
 template <bool kVec>

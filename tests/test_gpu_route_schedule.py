@@ -16,7 +16,14 @@ TOKEN = [dict(E=256, k=8, NB=1, bs=32), dict(E=256, k=8, NB=2, bs=32), dict(E=25
          dict(E=48, k=5, NB=4, bs=13), dict(E=16, k=1, NB=7, bs=3), dict(E=9, k=9, NB=3, bs=9)]
 BLOCK = [dict(E=64, k=8, NB=2, bs=5), dict(E=64, k=8, NB=64, bs=4), dict(E=64, k=8, NB=65, bs=4),
          dict(E=256, k=8, NB=3, bs=64), dict(E=256, k=8, NB=2, bs=72), dict(E=256, k=8, NB=2, bs=80),
-         dict(E=300, k=17, NB=5, bs=24), dict(E=512, k=3, NB=6, bs=9)]
+         dict(E=300, k=17, NB=5, bs=24), dict(E=512, k=3, NB=6, bs=9),
+         # both sides of the lines between one workgroup per block and separate launches
+         dict(E=219, k=8, NB=3, bs=16), dict(E=219, k=8, NB=3, bs=17), dict(E=219, k=8, NB=6, bs=64),
+         dict(E=301, k=5, NB=2, bs=8), dict(E=301, k=5, NB=2, bs=9), dict(E=301, k=5, NB=1, bs=16),
+         dict(E=301, k=5, NB=1, bs=17), dict(E=101, k=4, NB=1, bs=32), dict(E=101, k=4, NB=1, bs=33),
+         dict(E=128, k=6, NB=4, bs=32), dict(E=128, k=6, NB=4, bs=33), dict(E=128, k=6, NB=1, bs=64),
+         dict(E=128, k=6, NB=1, bs=65), dict(E=192, k=8, NB=2, bs=64), dict(E=192, k=8, NB=2, bs=65),
+         dict(E=188, k=8, NB=2, bs=33)]
 
 
 def _snapshot(m, routing, rows):
