@@ -264,8 +264,8 @@ dmoe_status dmoe_build_expert_schedule(const int32_t* experts, int n_groups, int
  *   dmoe_block_aggregate_topk(probs, n_blocks, block_size, E, k, ...)
  *   dmoe_build_expert_schedule(block_experts, n_blocks, block_size, k, E, sched)
  * with T = n_blocks*block_size, arguments as documented there, and results
- * bit-identical to that sequence.  Where it is faster (blocks of up to 16 to 64
- * tokens, by their number and E), a forward of one block runs as two kernels
+ * bit-identical to that sequence.  Where it is faster (blocks of up to 8 to 64
+ * tokens, by their number, E and type), a forward of one block runs as two kernels
  * and one of several blocks as three, instead of four.
  * Limits: the union of the three calls' limits (E <= 512).
  */

@@ -5,7 +5,7 @@
 //
 // A decode step routes few tokens; its routing kernels are bound by memory
 // round trips (each kernel boundary adds a write, a cache flush and a re-read
-// from another XCD), not by arithmetic.  Blocks of up to 16 to 64 tokens
+// from another XCD), not by arithmetic.  Blocks of up to 8 to 64 tokens
 // (route_block_fits) run everything after the router in one workgroup each
 // with a single round trip: all partial logits are loaded at once, then softmax
 // rows (into LDS), block sums, top-k and combine weights run on chip, and for
@@ -171,9 +171,9 @@ __global__ __launch_bounds__(kThreads) void route_small_kernel(
 // One workgroup per block when a block's rows fit in LDS and it is faster than
 // separate softmax and block top-k launches, which spread the rows over the
 // chip: its eight waves take the rows four at a time, so it pays by the row,
-// and more for rows that are not 16-byte aligned (scalar loads).  Routing of
-// blocks over E experts (hidden 512 to 2048, top-8), us, one workgroup /
-// separate:
+// and more for rows that are not 16-byte aligned (scalar loads), above all of
+// several partial planes (bf16 routers; fp32 ones have one).  Routing of blocks
+// over E experts (bf16, hidden 512 to 2048, top-8), us, one workgroup / separate:
 //   aligned, E = 256: 2 x 32 15.9 / 18.2, 2 x 64 19.0 / 19.9, 64 x 64 25.7 / 30.6,
 //     2 x 96 22.6 / 22.0; E = 192: 2 x 48 19.5 / 19.5, 24 x 64 26.0 / 27.2; E = 128:
 //     2 x 32 17.3 / 17.9, 2 x 48 19.9 / 19.0, 8 x 128 31.3 / 25.2
@@ -182,9 +182,13 @@ __global__ __launch_bounds__(kThreads) void route_small_kernel(
 //     E = 128: 48 17.1 / 18.6, 64 18.5 / 18.9, 96 23.1 / 21.1; not aligned, E = 101:
 //     32 15.8 / 17.1, 64 21.5 / 19.0; E = 219: 32 19.1 / 18.6; E = 301: 16 17.7 /
 //     20.9, 32 24.5 / 21.8
-static bool route_block_fits(int G, int gs, int E, int k) {
+//   fp32 (hidden 256), aligned, E = 128: 8 x 48 21.1 / 21.4, 8 x 64 22.0 / 22.0, 8 x 96
+//     29.1 / 27.8; not aligned, E = 161: 8 x 40 21.5 / 22.3, 2 x 64 21.6 / 21.2; E =
+//     219: 8 x 64 27.2 / 26.6, one block of 64 19.1 / 20.8, of 96 23.4 / 23.1
+static bool route_block_fits(dmoe_dtype dt, int G, int gs, int E, int k) {
   if (E > dev::kRegSoftmaxMaxE || k > dev::kMaxK) return false;
   if (fused_layout(gs, E, k).total * sizeof(float) > kMaxLdsBytes) return false;
+  if (dt == DMOE_F32) return gs <= (E % 4 && G > 1 ? 40 : 64);
   if (E % 4) return gs * (E > 256 ? 2 : 1) <= (G == 1 ? 32 : 16);
   return gs <= (G == 1 || E >= 192 ? 64 : 32);
 }
@@ -219,7 +223,7 @@ static hipError_t launch_route_topp(const RouteArgs& a, dmoe_dtype dt, hipStream
 hipError_t launch_route(const RouteArgs& a, dmoe_dtype dt, hipStream_t s) {
   if (a.topp) return launch_route_topp(a, dt, s);
   const int G = a.block ? a.T / a.gs : a.T;
-  if (a.block && route_block_fits(G, a.gs, a.E, a.k)) {
+  if (a.block && route_block_fits(dt, G, a.gs, a.E, a.k)) {
     float* part = nullptr;
     int S = 1;
     hipError_t err = launch_router_partials(a.x, a.w, dt, a.T, a.H, a.E, a.probs, a.x_chunked, a.workspace,

@@ -66,3 +66,19 @@ def test_routing_launch_sizes(gpu_lib, routing, over):
         fused.sched.n_work.fill_(3)
         g.replay()
         check()
+
+
+@pytest.mark.parametrize("E,NB,bs", [(161, 2, 40), (161, 2, 41), (161, 1, 64), (161, 1, 65), (128, 3, 64), (128, 3, 65)])
+def test_block_routing_launch_sizes_f32(gpu_lib, E, NB, bs):
+    """The fp32 lines between one workgroup per block and separate launches."""
+    cfg = get_config("small_f32").with_(name="rs32", H=96, E=E, I=16, I_s=0, k=5, NB=NB, bs=bs)
+    print("case", E, NB, bs, flush=True)
+    mk = lambda: MoELayer(cfg.H, cfg.E, cfg.I, cfg.I_s, cfg.k, cfg.NB, cfg.bs, dtype=torch.float32, device="cuda")  # noqa: E731
+    fused, chain = mk(), mk()
+    for seed in (0, 1):
+        d = make_inputs(cfg, seed=seed, device="cuda")
+        fused.route(d["x"], d["w_router"], None, "block", fused=True)
+        chain.route(d["x"], d["w_router"], None, "block", fused=False)
+        torch.cuda.synchronize()
+        for i, (a, b) in enumerate(zip(_snapshot(fused, "block", cfg.T * cfg.k), _snapshot(chain, "block", cfg.T * cfg.k))):
+            assert torch.equal(a, b), i
