@@ -48,11 +48,15 @@ struct F32Params {
   const float *w13, *w2, *ws13, *ws2;
   const int *n_work, *work, *row_token, *row_slot;
   int T, H, E, I, I_s, k, Tk, max_work, ldh;
+  int base;         // first unit (output feature) of the launch (size_t offsets only; 8 bytes more of arguments cost 0.2 us)
   float* hbuf;      // SwiGLU activations [Tk (+ T)][ldh]
   float* slot_out;  // [T][k][H]
   float* shared_out;
-  int base;         // first unit (output feature) of the launch
 };
+
+// Units and output features past a row's end pass 2^31 only in the widest layers.
+template <typename Off>
+using Unit = std::conditional_t<(sizeof(Off) > 4), unsigned, int>;
 
 // One burst of a wave's operands: NM weight matrices (gate and up, or down
 // alone), NT tiles of 16 tokens.
@@ -197,12 +201,12 @@ __device__ __forceinline__ void zero_f32(f32x4 (&acc)[NM][U][NT]) {
 
 // One pass of the gate/up kernel: 16*NT rows of the item from row p0.
 template <int U, int NT, bool kStream, typename Off>
-__device__ __forceinline__ void gateup_pass(const F32Params& p, const Group& g, int Iw, int u0, int p0, f32x4* red) {
+__device__ __forceinline__ void gateup_pass(const F32Params& p, const Group& g, int Iw, Unit<Off> u0, int p0, f32x4* red) {
   const int wave = threadIdx.x >> 6;
   const int lane = threadIdx.x & 63, q = lane >> 4, c = lane & 15;
   const float* W = g.expert >= 0 ? p.w13 + static_cast<size_t>(g.expert) * 2 * p.I * p.H : p.ws13;
   const size_t ldw = 2 * static_cast<size_t>(Iw);
-  const int uc = u0 + min(U * c, Iw - U - u0);  // units past the last: the last ones again, not stored
+  const int uc = min<Unit<Off>>(u0 + U * c, Iw - U);  // units past the last: the last ones again, not stored
   const float* const pw[2] = {W, W + Iw};
   const Off lo = 4 * q * static_cast<Off>(ldw) + uc;
   const float* pb[NT];
@@ -226,19 +230,19 @@ __device__ __forceinline__ void gateup_pass(const F32Params& p, const Group& g, 
       float* dst = p.hbuf + static_cast<size_t>(g.r0 + col) * p.ldh;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int du = U * (4 * q + r);
+        const Unit<Off> u1 = u0 + U * (4 * q + r);
         float h[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) h[u] = silu_f32(acc[0][u][ct][r]) * acc[1][u][ct][r];
-        if (du < Iw - u0) {  // I % U == 0: the U units lie wholly in or past the row
+        if (u1 < static_cast<Unit<Off>>(Iw)) {  // I % U == 0: the U units lie wholly in or past the row
           if constexpr (U > 1) {
             typedef float vec __attribute__((ext_vector_type(U)));
             vec v;
 #pragma unroll
             for (int u = 0; u < U; ++u) v[u] = h[u];
-            *reinterpret_cast<vec*>(dst + u0 + du) = v;
+            *reinterpret_cast<vec*>(dst + u1) = v;
           } else {
-            dst[u0 + du] = h[0];
+            dst[u1] = h[0];
           }
         }
       }
@@ -278,8 +282,8 @@ __global__ __launch_bounds__(kThreads, 2) void ffn_gateup_f32_kernel(F32Params p
   Group g;
   if (!decode_item(blockIdx.y, 0, p.max_work, p.n_work, p.work, p.row_token, p.T, p.Tk, p.E, g)) return;
   const int Iw = g.expert >= 0 ? p.I : p.I_s;
-  const int u0 = p.base + blockIdx.x * 16 * U;
-  if (u0 >= Iw) return;
+  const Unit<Off> u0 = (sizeof(Off) > 4 ? p.base : 0) + blockIdx.x * 16 * U;
+  if (u0 >= static_cast<Unit<Off>>(Iw)) return;
   const int p0 = blockIdx.z * kPassRows;
   if (p0 >= g.n) return;
   by_rows<kStream>(g, p0, [&](auto nt, auto stream) {
@@ -288,12 +292,12 @@ __global__ __launch_bounds__(kThreads, 2) void ffn_gateup_f32_kernel(F32Params p
 }
 
 template <int U, int NT, bool kStream, bool kVecB, typename Off>
-__device__ __forceinline__ void down_pass(const F32Params& p, const Group& g, int Kd, int j0, int p0, f32x4* red) {
+__device__ __forceinline__ void down_pass(const F32Params& p, const Group& g, int Kd, Unit<Off> j0, int p0, f32x4* red) {
   const int wave = threadIdx.x >> 6;
   const int lane = threadIdx.x & 63, q = lane >> 4, c = lane & 15;
   const int H = p.H;
   const float* W = g.expert >= 0 ? p.w2 + static_cast<size_t>(g.expert) * H * p.I : p.ws2;
-  const int jc = j0 + min(U * c, H - U - j0);
+  const int jc = min<Unit<Off>>(j0 + U * c, H - U);
   const float* const pw[1] = {W};
   const Off lo = 4 * q * static_cast<Off>(H) + jc;
   const float* pb[NT];
@@ -315,13 +319,13 @@ __device__ __forceinline__ void down_pass(const F32Params& p, const Group& g, in
                          : p.shared_out + static_cast<size_t>(g.t0 + col) * H;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int dj = U * (4 * q + r);
+        const Unit<Off> j1 = j0 + U * (4 * q + r);
         if constexpr (U == 4) {
-          if (dj < H - j0)
-            *reinterpret_cast<f32x4*>(dst + j0 + dj) =
+          if (j1 < static_cast<Unit<Off>>(H))
+            *reinterpret_cast<f32x4*>(dst + j1) =
                 f32x4{acc[0][0][ct][r], acc[0][1][ct][r], acc[0][2][ct][r], acc[0][3][ct][r]};  // H % 4 == 0
         } else {
-          if (dj < H - j0) dst[j0 + dj] = acc[0][0][ct][r];
+          if (j1 < static_cast<Unit<Off>>(H)) dst[j1] = acc[0][0][ct][r];
         }
       }
     }
@@ -336,7 +340,7 @@ __global__ __launch_bounds__(kThreads, 2) void ffn_down_f32_kernel(F32Params p) 
   Group g;
   if (!decode_item(blockIdx.y, 0, p.max_work, p.n_work, p.work, p.row_token, p.T, p.Tk, p.E, g)) return;
   const int Kd = g.expert >= 0 ? p.I : p.I_s;
-  const int j0 = p.base + blockIdx.x * 16 * U;
+  const Unit<Off> j0 = (sizeof(Off) > 4 ? p.base : 0) + blockIdx.x * 16 * U;
   const int p0 = blockIdx.z * kPassRows;
   if (p0 >= g.n) return;
   by_rows<kStream>(g, p0, [&](auto nt, auto stream) {
@@ -359,8 +363,8 @@ constexpr int kMaxGridX = 1 << 23;
 hipError_t launch_ffn_f32(const FfnArgs& a, int ldh, int items, hipStream_t s) {
   F32Params p{static_cast<const float*>(a.x), static_cast<const float*>(a.xr), static_cast<const float*>(a.w13), static_cast<const float*>(a.w2),
               static_cast<const float*>(a.ws13), static_cast<const float*>(a.ws2), a.sched.n_work, a.sched.work,
-              a.sched.row_token, a.sched.row_slot, a.T, a.H, a.E, a.I, a.I_s, a.k, a.T * a.k, a.max_work, ldh,
-              static_cast<float*>(a.workspace), static_cast<float*>(a.slot_out), a.shared_out, 0};
+              a.sched.row_token, a.sched.row_slot, a.T, a.H, a.E, a.I, a.I_s, a.k, a.T * a.k, a.max_work, ldh, 0,
+              static_cast<float*>(a.workspace), static_cast<float*>(a.slot_out), a.shared_out};
   // Items of few rows read their weights once per launch: non-temporal loads
   // (by_rows), where the weights of all items, an upper bound of what is read,
   // exceed 128 MiB.  Layers in rotation, so that weights come from HBM, us per
@@ -376,7 +380,9 @@ hipError_t launch_ffn_f32(const FfnArgs& a, int ldh, int items, hipStream_t s) {
   // A lane's weight offset, 12 rows and a row's units at most, in 32 bits unless
   // the layer is wider than any (three blocks of 32 tokens over 72 experts,
   // hidden 360, intermediate 376: 60.8 us per layer against 62.7 with 64 bits).
-  const bool big = 13 * std::max(2 * static_cast<long>(ldh), static_cast<long>(a.H)) > (1L << 32) - 1;
+  // Such a layer may also need more than one launch.
+  const bool big = 13 * std::max(2 * static_cast<long>(ldh), static_cast<long>(a.H)) > (1L << 32) - 1 ||
+                   std::max(ldh, a.H) > 16 * kMaxGridX;
   const bool wide_ok = a.I % kWideGu == 0 && a.I_s % kWideGu == 0;  // aligned loads and stores
   const bool wide = wide_ok && (static_cast<long>(ldh) + 16 * kWideGu - 1) / (16 * kWideGu) * items >= kFillGroups;
   // an item holds each token at most once
