@@ -341,9 +341,10 @@ __device__ __forceinline__ bool map_item(const FfnParams& p, int gx, int& item, 
 // decode kernels.
 //
 // What bounds it: what a CU can have in flight to L2 and HBM.  Counters at 64
-// blocks of 64 tokens (hidden 2048, 256 experts of intermediate 512; gate/up
-// 255 us): matrix cores busy 28 %, L2-to-CU 2.75 GB (about 45 GB/s per CU
-// at an average request latency of 550 cycles), HBM side 1.27 GB; reading the
+// blocks of 64 tokens (hidden 2048, 256 experts of intermediate 512; wide
+// gate/up 225 us, down 146): 28 and 21 % of the dense bf16 peak, 1.18 and 0.55 GB
+// read from the fabric (5.2 and 3.8 TB/s), waves waiting for loads or barriers
+// 48 and 50 % of their cycles, for an issue slot 41 and 36 %; reading the
 // LDS fragments one, two or three tiles ahead measured the same.  Token
 // fragments two stages ahead without registers, instead of one stage ahead
 // through registers: that layer 508 -> 490 us, 16 x 32 tokens 173 -> 164,

@@ -293,7 +293,11 @@ constexpr int kRTof = NT <= 2 ? 2 : 1;
 // 1024, 1280, 768 or 1792; or the whole of 256 or 512) run straight-line, tokens
 // and weights issued alternately.  Measured, us per layer of the decode
 // shape, against bursts with two token buffers: 28.4 -> 27.9, at hidden 4096
-// 50.7 -> 48.1, at 1024 24.4 -> 23.7.  Loading the first token chunk or two
+// 50.7 -> 48.1, at 1024 24.4 -> 23.7; 64 experts, hidden 1536 to 3840, 32 tokens
+// 27.5 -> 27.2, 30.5 -> 29.6 (1792), 40.5 -> 39.7 (3072), 45.3 -> 45.5 (3584), 52.2
+// -> 51.4.  Layers of few workgroups lost 0.3 to 0.5 (48 experts, intermediate 256,
+// top-4: hidden 1280 21.2 -> 21.5, 1792 23.5 -> 24.2), with bursts of 16 at those
+// sizes just as much.  Loading the first token chunk or two
 // before the routing spilled them (30.5, 34.7).
 template <int NT, int RT>
 __device__ __forceinline__ void gateup_dot(const bf16_t* pa, uint32_t la, size_t tstride, const bf16_t* pb,
