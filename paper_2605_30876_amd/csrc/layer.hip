@@ -288,42 +288,27 @@ template <int NT>
 constexpr int kRTof = NT <= 2 ? 2 : 1;
 
 // acc += the wave's K-slice of RT gate/up tiles over NT token tiles: weights
-// at pa + la, tokens at pb + lb[ct] (uniform base + lane offset).  Slices of
-// whole bursts (16 K-steps per wave: H a multiple of 2048; else 8, 10, 6 or 7: of
-// 1024, 1280, 768 or 1792; or the whole of 256 or 512) run straight-line, tokens
-// and weights issued alternately.  Measured, us per layer of the decode
-// shape, against bursts with two token buffers: 28.4 -> 27.9, at hidden 4096
-// 50.7 -> 48.1, at 1024 24.4 -> 23.7; 64 experts, hidden 1536 to 3840, 32 tokens
-// 27.5 -> 27.2, 30.5 -> 29.6 (1792), 40.5 -> 39.7 (3072), 45.3 -> 45.5 (3584), 52.2
-// -> 51.4.  Layers of few workgroups lost 0.3 to 0.5 (48 experts, intermediate 256,
-// top-4: hidden 1280 21.2 -> 21.5, 1792 23.5 -> 24.2), with bursts of 16 at those
-// sizes just as much.  Loading the first token chunk or two
+// at pa + la, tokens at pb + lb[ct] (uniform base + lane offset).  K > 0: bursts
+// of K K-steps, straight-line, tokens and weights issued alternately; 0: bursts
+// of 16 with two token buffers and a shorter last one (gateup_burst chooses).
+// Measured, us per layer of the decode shape, straight-line against two token
+// buffers: 28.4 -> 27.9, at hidden 4096 50.7 -> 48.1, at 1024 24.4 -> 23.7.  Each
+// kernel holds one of them: with the choice inside, the code of all was 0.1
+// to 0.4 us slower (48 experts of intermediate 256, top-6, 16 tokens: hidden 1792
+// 23.0 -> 22.6, 4096 26.8 -> 26.1).  Loading the first token chunk or two
 // before the routing spilled them (30.5, 34.7).
-template <int NT, int RT>
+template <int K, int NT, int RT>
 __device__ __forceinline__ void gateup_dot(const bf16_t* pa, uint32_t la, size_t tstride, const bf16_t* pb,
                                            const uint32_t (&lb)[NT], int bstep, int steps, f32x4 (&acc)[RT][NT]) {
-  if constexpr (NT <= 2) {
-    if (steps % 16 == 0) {
-      fdev::WaveOps3<NT, 16, 4, RT> w;
-      for (int sc = 0; sc < steps; sc += 16)
-        fdev::wave_dot_burst<true>(w, pa + sc * kFrag, la, tstride, pb + sc * bstep, lb, bstep, acc);
-      return;
-    }
-#define DMOE_SHORT(K_)                                                                                            \
-  if (steps % K_ == 0) {                                                                                          \
-    for (int sc = 0; sc < steps; sc += K_)                                                                        \
-      fdev::wave_dot_short<true, K_>(pa + sc * kFrag, la, tstride, pb + sc * bstep, lb, bstep, acc);              \
-    return;                                                                                                       \
-  }
-    DMOE_SHORT(8)
-    DMOE_SHORT(10)
-    DMOE_SHORT(6)
-    DMOE_SHORT(7)
-    if (steps <= 4) {  // H of 256 or 512
-      DMOE_SHORT(4)
-      DMOE_SHORT(2)
-    }
-#undef DMOE_SHORT
+  if constexpr (K == 16) {
+    fdev::WaveOps3<NT, 16, 4, RT> w;
+    for (int sc = 0; sc < steps; sc += 16)
+      fdev::wave_dot_burst<true>(w, pa + sc * kFrag, la, tstride, pb + sc * bstep, lb, bstep, acc);
+    return;
+  } else if constexpr (K > 0) {
+    for (int sc = 0; sc < steps; sc += K)
+      fdev::wave_dot_short<true, K>(pa + sc * kFrag, la, tstride, pb + sc * bstep, lb, bstep, acc);
+    return;
   }
   const bf16_t* pl[NT];
 #pragma unroll
@@ -333,7 +318,7 @@ __device__ __forceinline__ void gateup_dot(const bf16_t* pa, uint32_t la, size_t
 }
 
 // The shared expert's gate/up tiles over all T tokens (chunk-major x).
-template <int NT>
+template <int K, int NT>
 __device__ void shared_gateup_tiles(const LayerParams& p, int it0, f32x4 (*red)[kRTof<NT>][NT][kWave]) {
   constexpr int kRT = kRTof<NT>;
   const int T = p.T, H = p.H;
@@ -347,7 +332,7 @@ __device__ void shared_gateup_tiles(const LayerParams& p, int it0, f32x4 (*red)[
   for (int ct = 0; ct < NT; ++ct) lb[ct] = (q * T + min(ct * kTok + c, T - 1)) * 8;
   f32x4 acc[kRT][NT];
   fdev::zero(acc);
-  gateup_dot<NT, kRT>(pa, lane * 8, static_cast<size_t>(ksteps) * kFrag, pb, lb, 32 * T, steps, acc);
+  gateup_dot<K, NT, kRT>(pa, lane * 8, static_cast<size_t>(ksteps) * kFrag, pb, lb, 32 * T, steps, acc);
   fdev::reduce_waves(acc, red, wave, lane);
   if (wave != 0) return;
 #pragma unroll
@@ -359,7 +344,7 @@ __device__ void shared_gateup_tiles(const LayerParams& p, int it0, f32x4 (*red)[
     }
 }
 
-template <int NQ, int NT>
+template <int NQ, int NT, int K>
 __global__ __launch_bounds__(kThreads, 2) void layer_route_gateup_kernel(LayerParams p) {
   extern __shared__ float lds[];
   __shared__ int sel[kRoundsMax];
@@ -376,7 +361,7 @@ __global__ __launch_bounds__(kThreads, 2) void layer_route_gateup_kernel(LayerPa
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int it = blockIdx.x * kRT, j = blockIdx.y;
   if (j == k) {  // the shared expert: no routing needed
-    if (it * 8 < p.I_s) shared_gateup_tiles<NT>(p, it, red);
+    if (it * 8 < p.I_s) shared_gateup_tiles<K, NT>(p, it, red);
     return;
   }
   if (it * 8 >= p.I) return;  // past this expert's tiles (I < I_s)
@@ -421,7 +406,7 @@ __global__ __launch_bounds__(kThreads, 2) void layer_route_gateup_kernel(LayerPa
   const bf16_t* pa = W + (static_cast<size_t>(it) * ksteps + uw * steps) * kFrag;
   f32x4 acc[kRT][NT];
   fdev::zero(acc);
-  gateup_dot<NT, kRT>(pa, lane * 8, static_cast<size_t>(ksteps) * kFrag, pb, lb, 32 * T, steps, acc);
+  gateup_dot<K, NT, kRT>(pa, lane * 8, static_cast<size_t>(ksteps) * kFrag, pb, lb, 32 * T, steps, acc);
 
   // 6. the routing outputs (workgroup (0, 0), while the other workgroups
   //    stream): the selection, gap, every token's combine weights (its
@@ -542,6 +527,21 @@ __global__ __launch_bounds__(kMaxSegments * kWave) void layer_down_combine_kerne
   }
 }
 
+// The straight-line burst of slices of `steps` K-steps, or 0 (12, 22, 26, 28 and
+// 30 steps, and longer ones that 8 does not divide): us per layer, two token buffers / straight-line, 48 experts, top-2, 32 tokens:
+// hidden 1536 (12 steps: two of 6) 20.0 / 20.3, 3584 (four of 7) 28.8 / 29.1, 3840
+// (three of 10) 33.2 / 34.0; the other way round at 64 experts of intermediate
+// 640, top-8, 16 tokens: 1280 (one of 10) 28.4 / 28.4, 1792 (two of 7) 32.8 / 31.7,
+// 2304 (three of 6) 36.2 / 35.4, 2560 (two of 10) 35.6 / 35.4.
+int gateup_burst(int steps) {
+  if (steps % 16 == 0) return 16;
+  if (steps % 8 == 0) return 8;
+  if (steps == 10 || steps == 20) return 10;
+  if (steps == 6 || steps == 18) return 6;
+  if (steps == 14) return 7;
+  return steps == 4 || steps == 2 ? steps : 0;
+}
+
 template <int NT>
 hipError_t launch_nt(const LayerParams& p, dmoe_dtype y_dt, hipStream_t s) {
   const int n_router = ((p.T + kTok - 1) / kTok) * ((p.E + kTok - 1) / kTok);
@@ -550,10 +550,25 @@ hipError_t launch_nt(const LayerParams& p, dmoe_dtype y_dt, hipStream_t s) {
   if (err != hipSuccess) return err;
   const size_t lds = prologue_words(p.T, p.E) * sizeof(float);
   const dim3 gu_grid(std::max(p.I, p.ws13 ? p.I_s : 0) / (8 * kRTof<NT>), p.k + (p.ws13 ? 1 : 0));
-  if (p.E <= 256)
-    layer_route_gateup_kernel<1, NT><<<gu_grid, kThreads, lds, s>>>(p);
-  else
-    layer_route_gateup_kernel<2, NT><<<gu_grid, kThreads, lds, s>>>(p);
+  const int burst = NT <= 2 ? gateup_burst(p.H / 128) : 0;
+#define DMOE_GATEUP(K_)                                                       \
+  if (burst == K_) {                                                          \
+    if (p.E <= 256)                                                           \
+      layer_route_gateup_kernel<1, NT, K_><<<gu_grid, kThreads, lds, s>>>(p); \
+    else                                                                      \
+      layer_route_gateup_kernel<2, NT, K_><<<gu_grid, kThreads, lds, s>>>(p); \
+  }
+  DMOE_GATEUP(0)
+  if constexpr (NT <= 2) {
+    DMOE_GATEUP(16)
+    DMOE_GATEUP(8)
+    DMOE_GATEUP(10)
+    DMOE_GATEUP(6)
+    DMOE_GATEUP(7)
+    DMOE_GATEUP(4)
+    DMOE_GATEUP(2)
+  }
+#undef DMOE_GATEUP
   err = hipGetLastError();
   if (err != hipSuccess) return err;
   const int waves = p.k + (p.ws13 ? 1 : 0);

@@ -1,6 +1,6 @@
 """The one-block layer at hidden sizes that take each of its gate/up bursts
 (one or several of 2, 4, 6, 7, 8, 10 and 16 K-steps per wave, and the bursts
-of up to 16 with a shorter last one that other sizes take: 22 and 26 steps),
+of up to 16 with a shorter last one that 12, 22, 26, 28 and 30 steps take),
 one and two token tiles, with and without a router bias and a shared expert.
 Against the CPU oracle, bf16 tolerance (2e-2 of the output's RMS)."""
 import pytest
