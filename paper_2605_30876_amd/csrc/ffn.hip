@@ -342,7 +342,7 @@ __device__ __forceinline__ bool map_item(const FfnParams& p, int gx, int& item, 
 //
 // What bounds it: what a CU can have in flight to L2 and HBM.  Counters at 64
 // blocks of 64 tokens (hidden 2048, 256 experts of intermediate 512; wide
-// gate/up 225 us, down 146): 28 and 21 % of the dense bf16 peak, 1.18 and 0.55 GB
+// gate/up 226 us, down 147): 27 and 21 % of the dense bf16 peak, 1.18 and 0.55 GB
 // read from the fabric (5.2 and 3.8 TB/s), waves waiting for loads or barriers
 // 48 and 50 % of their cycles, for an issue slot 41 and 36 %; reading the
 // LDS fragments one, two or three tiles ahead measured the same.  Token
